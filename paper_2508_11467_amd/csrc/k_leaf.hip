@@ -1,15 +1,14 @@
 // Leaf solves of the divide-and-conquer tree (Algorithm 2 step (1): the
 // bottom subproblems by QR iteration).
 //
-// One 64-lane wavefront per leaf of m <= 32 rows and m+s columns.  The
-// bidiagonal lives in LDS; every lane computes the same scalar Givens
-// sequence (implicit-shift Golub-Kahan sweeps with a Wilkinson shift, zero
-// diagonal chasing), and lane r applies each rotation to row r of the
-// accumulated W (m x m) and Q ((m+s) x (m+s)), stored column-major in LDS so
-// the 64 lanes touch consecutive words.  The leaf is first scaled by a power
-// of two so no square can overflow; the values are scaled back on output.
-// Output columns are written sorted by value (ascending); each physical
-// column records the leaf's row range as its support.
+// One workgroup per leaf of m <= 32 rows and m+s columns: implicit-shift
+// Golub-Kahan sweeps with a Wilkinson shift, zero diagonal chasing, the
+// accumulated W (m x m) and Q ((m+s) x (m+s)) stored column-major in LDS so
+// that a wavefront's lanes (a row each) touch consecutive words.  The leaf is
+// first scaled by a power of two so no square can overflow; the values are
+// scaled back on output.  Output columns are written sorted by value
+// (ascending); each physical column records the leaf's row range as its
+// support.
 #include "bdc_internal.h"
 
 namespace bdc {
@@ -50,6 +49,19 @@ __device__ inline void givens(double f, double g, double& c, double& s, double& 
   }
 }
 
+// The same without its careful branches: what givens() returns
+// where g != 0 and f^2 + g^2 > 2^-960.
+__device__ inline void givens_fast(double f, double g, double& c, double& s, double& r) {
+  const double q = fma(f, f, g * g);
+  double y = __builtin_amdgcn_rsq(q);
+  const double hq = 0.5 * q;
+  y = y * fma(-hq * y, y, 1.5);
+  y = y * fma(-hq * y, y, 1.5);
+  c = f * y;
+  s = g * y;
+  r = q * y;
+}
+
 // columns (i, j) of an LDS matrix (column stride ld) <- (c a_i + s a_j,
 // -s a_i + c a_j), row = lane
 __device__ inline void rot_cols(double* A, int ld, int rows, int i, int j, double c, double s, int lane) {
@@ -66,31 +78,118 @@ __device__ inline double wave_max(double v) {
   return v;
 }
 
-// One 64-lane wavefront per leaf.  Lane L holds d_L and e_L (the
-// superdiagonal entry right of d_L) in registers; the Givens chain runs on
-// wave-uniform values read with readlane, and each rotation of W and Q is
-// applied by lane r to row r of the column-major LDS copies.  Along a sweep
-// the column being rotated forward stays in a register, so each step reads
-// one new column (independent of the chain) and writes one.
-// The LDS copies are sized for leaves of at most ML rows, so launches of
-// small leaves fit more wavefronts per CU (the chain is latency-bound, and a
-// batch has many leaves per SIMD).
+// Two wavefronts per leaf.  Wavefront 0 runs the Givens chain of a sweep and
+// leaves its rotations in LDS; wavefront 1 does the rest: the tests before a
+// sweep (lane i holds d_i and e_i, the superdiagonal entry right of d_i), the
+// shift, the rare rotations that are no sweep, and, while the next sweep's
+// chain runs, the last sweep's rotations of W and Q (lane r: row r of the
+// column-major LDS copies; the column being rotated forward stays in a
+// register).
+//
+// The chain bounds the time: 38 FP64 operations and two reciprocal square
+// roots a step, about 1150 steps for a 32-row leaf, on one wavefront.  So it
+// holds nothing else: no test (each step's rotations take givens()' usual
+// path; a rotation that would not have shows afterwards by s = 0 or a tiny r,
+// and wavefront 1 redoes such a sweep step by step), no cross-lane read, and
+// no update of W or Q.  Measured (leaves of 16..32 rows): the leaves of n =
+// 100 155 us, of n = 1000 237 and of n = 16384 280, against 260, 443 and 555
+// for one wavefront doing everything with a test per rotation (about 345
+// against 900 cycles a step); 40000 leaves of a batch, which fill the chip
+// either way, 4.8 against 6.2 ms.  Several leaves per chain wavefront (a lane
+// each) measured slower in both regimes (322-369 us and 6.2-8 ms): lanes wait
+// for the longest block.
 template <int ML>
-__global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves, Work w) {
-  constexpr int kLd = ML + 1;  // LDS column stride (doubles)
-  __shared__ double W[ML * kLd];
-  __shared__ double Q[(ML + 1) * kLd];
+struct LeafLds {
+  static constexpr int kLd = ML + 1;  // column stride (doubles)
+  double W[ML * kLd];
+  double Q[(ML + 1) * kLd];
+  struct Sweep {            // one posted sweep, by parity
+    double2 in[ML + 2];     // (d_i, e_i) before it
+    double2 out[ML + 2];    // (d_i, e_{i-1}) after it
+    double2 rq[ML + 2];     // (c, s) of the rotation of Q's (W's) columns (k, k+1),
+    double2 rw[ML + 2];
+  } sw[2];
+  double2 yz;               // the first rotation's two entries
+  int lo, hi;               // the sweep's block; hi = 0: no more sweeps
+};
+
+// one sweep's chain on the entries of `in`: steps lo .. lo + n - 1
+template <int ML>
+__device__ inline void leaf_chain(typename LeafLds<ML>::Sweep& S, int lo, int n, double y, double z) {
+  const double2 v0 = S.in[lo], v1 = S.in[lo + 1];
+  double dk = v0.x, ek = v0.y, dk1 = v1.x, ek1 = v1.y;
+  typename LeafLds<ML>::Sweep* p = reinterpret_cast<typename LeafLds<ML>::Sweep*>(&S.in[lo]);  // moves with k
+#pragma unroll 2
+  for (int k = 0; k < n; ++k) {
+    const double2 v2 = p->in[2];
+    double c, s, r, c2, s2, r2;
+    givens_fast(y, z, c, s, r);
+    const double ndk = fma(c, dk, s * ek);
+    const double bulge = s * dk1;
+    const double nek = fma(c, ek, -(s * dk));
+    const double ndk1 = c * dk1;
+    givens_fast(ndk, bulge, c2, s2, r2);
+    p->rq[0] = make_double2(c, s);
+    p->out[0] = make_double2(r2, r);
+    p->rw[0] = make_double2(c2, s2);
+    y = fma(nek, c2, ndk1 * s2);      // e_k
+    dk = fma(ndk1, c2, -(nek * s2));  // d_{k+1}
+    z = s2 * ek1;                     // the bulge right of e_k
+    ek = c2 * ek1;                    // e_{k+1} (ek1 = 0 at the block's end)
+    dk1 = v2.x;
+    ek1 = v2.y;
+    p = reinterpret_cast<typename LeafLds<ML>::Sweep*>(reinterpret_cast<double2*>(p) + 1);
+  }
+  p->out[0] = make_double2(dk, y);
+}
+
+// the rotations of one sweep on row `lane` of W and Q
+template <int ML>
+__device__ inline void leaf_apply(LeafLds<ML>& S, const typename LeafLds<ML>::Sweep& R, int lo, int hi, int lane) {
+  constexpr int kLd = LeafLds<ML>::kLd;
+  double* q = S.Q + lane;
+  double* w = S.W + lane;
+  double qk = q[lo * kLd], wk = w[lo * kLd];
+  for (int k = lo; k < hi; ++k) {
+    const double2 a = R.rq[k], b = R.rw[k];
+    const double qk1 = q[(k + 1) * kLd], wk1 = w[(k + 1) * kLd];
+    q[k * kLd] = fma(qk, a.x, a.y * qk1);
+    qk = fma(qk1, a.x, -(qk * a.y));
+    w[k * kLd] = fma(wk, b.x, b.y * wk1);
+    wk = fma(wk1, b.x, -(wk * b.y));
+  }
+  q[hi * kLd] = qk;
+  w[hi * kLd] = wk;
+}
+
+template <int ML>
+__global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leaves, Work w) {
+  constexpr int kLd = LeafLds<ML>::kLd;
+  __shared__ LeafLds<ML> S;
+  double* const W = S.W;
+  double* const Q = S.Q;
+  const int lane = threadIdx.x & 63;
+
+  if (threadIdx.x < 64) {
+    for (int par = 0;; par ^= 1) {
+      __syncthreads();
+      const int lo = __builtin_amdgcn_readfirstlane(S.lo), hi = __builtin_amdgcn_readfirstlane(S.hi);
+      if (hi == 0) return;
+      const double2 yz = S.yz;
+      if (lane == 0) leaf_chain<ML>(S.sw[par], lo, hi - lo, yz.x, yz.y);
+      __syncthreads();
+    }
+  }
 
   const LeafDesc L = leaves[blockIdx.x];
   const int m = L.m, s = L.s, ms = m + s, r0 = L.r0;
-  const int lane = threadIdx.x;
   const int64_t ld = L.ld;
   const int64_t pv = L.vec_off;
   unsigned long long nrot_w = 0, nrot_q = 0;  // rotations applied to W and to Q
+  const bool row = lane < ms;  // W's row m, which nothing reads, stands in for the row that W has not when s = 1
 
   for (int i = lane; i < ML * kLd; i += 64) W[i] = 0.0;
   for (int i = lane; i < (ML + 1) * kLd; i += 64) Q[i] = 0.0;
-  __syncthreads();
   if (lane < m) W[lane + lane * kLd] = 1.0;
   if (lane < ms) Q[lane + lane * kLd] = 1.0;
 
@@ -100,8 +199,8 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
   if (lane < m - 1 + s) ev = w.e[pv + r0 + lane];
   // every entry of d and e belongs to exactly one leaf or one merge's middle
   // row, so leaves and merges between them check all of the input
-  const bool bad = !(fabs(dv) <= 1.79769313486231570e308) || !(fabs(ev) <= 1.79769313486231570e308);
-  if (__any(bad) && lane == 0) atomicOr(&w.ctl->nonfinite, 1);
+  const bool bad = __any(!(fabs(dv) <= 1.79769313486231570e308) || !(fabs(ev) <= 1.79769313486231570e308));
+  if (bad && lane == 0) atomicOr(&w.ctl->nonfinite, 1);
   const double amax = wave_max(fmax(fabs(dv), fabs(ev)));
   double p = 1.0;
   if (amax > 0.0 && amax <= 1.79e308) {
@@ -112,7 +211,6 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
   double dreg = dv / p;  // d_lane
   double ereg = ev / p;  // e_lane (lane m-1: the extra column's entry when s = 1)
   const double tiny = kEps * (amax / p);
-  __syncthreads();
 
   // s = 1: remove the extra column's entry, bottom row first.  The right
   // rotation of columns (j, m) zeroes B[j, m] and moves a fill-in to B[j-1, m].
@@ -135,25 +233,76 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
 
   const int max_steps = w.max_leaf_sweeps * (m > 0 ? m : 1);
   int steps = 0;
-  int hi = m - 1;
-  while (hi > 0) {
-    // negligible superdiagonals -> 0; then the unreduced block [lo, hi]
-    const double dnext = __shfl_down(dreg, 1, 64);
-    if (lane < hi && fabs(ereg) <= kEps * (fabs(dreg) + fabs(dnext))) ereg = 0.0;
-    const unsigned long long nz = __ballot(lane < hi && ereg != 0.0);
-    if (!((nz >> (hi - 1)) & 1ull)) {
-      --hi;
-      continue;
+  int hi = m - 1, lo = 0;
+  double mu = 0.0;
+  bool go = false, pending = false;  // a sweep posted for this parity; the last sweep's rotations not applied yet
+  int phi = 0, plo = 0;
+  for (int par = 0;; par ^= 1) {
+    // the posted sweep's outcome, then the tests before the next one
+    if (go) {
+      const typename LeafLds<ML>::Sweep& R = S.sw[par ^ 1];
+      const double2 o0 = R.out[lane <= ML ? lane : 0], o1 = R.out[lane <= ML ? lane + 1 : 0];
+      const double sq = R.rq[lane <= ML ? lane : 0].y, sw = R.rw[lane <= ML ? lane : 0].y;
+      // s = 0 where g = 0 (or g / r underflowed); r < 2^-470 well before f^2 + g^2 <= 2^-960
+      const bool odd = lane >= lo && lane < hi && (sq == 0.0 || sw == 0.0 || !(o0.x > 0x1p-470) || !(o0.y > 0x1p-470));
+      if (__any(odd) || bad) {
+        // again from the entries as posted, every rotation by givens()
+        double dk = lane_val(dreg, lo), ek = lane_val(ereg, lo);
+        double y = fma(dk, dk, -mu), z = dk * ek;
+        for (int k = lo; k < hi; ++k) {
+          const double dk1 = lane_val(dreg, k + 1), ek1 = k < hi - 1 ? lane_val(ereg, k + 1) : 0.0;
+          double c, sn, r, c2, sn2, r2;
+          givens(y, z, c, sn, r);
+          if (k > lo && lane == k - 1) ereg = r;
+          const double ndk = fma(c, dk, sn * ek);
+          const double nek = fma(c, ek, -(sn * dk));
+          const double ndk1 = c * dk1;
+          givens(ndk, sn * dk1, c2, sn2, r2);
+          if (lane == k) dreg = r2;
+          if (lane == 0) {
+            S.sw[par ^ 1].rq[k] = make_double2(c, sn);
+            S.sw[par ^ 1].rw[k] = make_double2(c2, sn2);
+          }
+          y = fma(nek, c2, ndk1 * sn2);
+          dk = fma(ndk1, c2, -(nek * sn2));
+          z = sn2 * ek1;
+          ek = c2 * ek1;
+        }
+        if (lane == hi - 1) ereg = y;
+        if (lane == hi) dreg = dk;
+      } else {
+        if (lane >= lo && lane <= hi) dreg = o0.x;
+        if (lane >= lo && lane < hi) ereg = o1.y;
+      }
+      nrot_q += hi - lo;
+      nrot_w += hi - lo;
+      pending = true;
+      plo = lo;
+      phi = hi;
+      go = false;
     }
-    if (steps >= max_steps) {
-      if (lane == 0) atomicAdd(&w.ctl->leaf_capped, 1);
-      break;
-    }
-    ++steps;
-    const unsigned long long zero_below = ~nz & ((1ull << (hi - 1)) - 1ull);
-    const int lo = zero_below ? 64 - __builtin_clzll(zero_below) : 0;
-    const unsigned long long zd = __ballot(lane >= lo && lane <= hi && fabs(dreg) <= tiny);
-    if (zd) {
+    while (hi > 0) {
+      // negligible superdiagonals -> 0; then the unreduced block [lo, hi]
+      const double dnext = __shfl_down(dreg, 1, 64);
+      if (lane < hi && fabs(ereg) <= kEps * (fabs(dreg) + fabs(dnext))) ereg = 0.0;
+      const unsigned long long nz = __ballot(lane < hi && ereg != 0.0);
+      hi = nz ? 64 - __builtin_clzll(nz) : 0;
+      if (hi == 0) break;
+      if (steps >= max_steps) {
+        if (lane == 0) atomicAdd(&w.ctl->leaf_capped, 1);
+        hi = 0;
+        break;
+      }
+      ++steps;
+      const unsigned long long zero_below = ~nz & ((1ull << (hi - 1)) - 1ull);
+      lo = zero_below ? 64 - __builtin_clzll(zero_below) : 0;
+      const unsigned long long zd = __ballot(lane >= lo && lane <= hi && fabs(dreg) <= tiny);
+      if (!zd) {
+        go = true;
+        break;
+      }
+      if (pending && row) leaf_apply<ML>(S, S.sw[par ^ 1], plo, phi, lane);
+      pending = false;
       const int i = __builtin_ctzll(zd);
       if (lane == i) dreg = 0.0;
       if (i < hi) {
@@ -189,11 +338,9 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
           ++nrot_q;
         }
       }
-      continue;
     }
-    // Wilkinson shift: eigenvalue of the trailing 2x2 of B^T B nearer its end
-    double mu;
-    {
+    if (go) {
+      // Wilkinson shift: eigenvalue of the trailing 2x2 of B^T B nearer its end
       const double dm = lane_val(dreg, hi - 1), dn = lane_val(dreg, hi), fm = lane_val(ereg, hi - 1);
       const double g = (hi - 1 > lo) ? lane_val(ereg, hi - 2) : 0.0;
       const double t11 = dm * dm + g * g, t12 = dm * fm, t22 = dn * dn + fm * fm;
@@ -205,61 +352,22 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
         const double denom = delta + (delta >= 0.0 ? root : -root);
         mu = t22 - t12 * t12 / denom;
       }
+      if (lane <= ML) S.sw[par].in[lane] = make_double2(dreg, ereg);
+      const double dk = lane_val(dreg, lo);
+      if (lane == 0) S.yz = make_double2(fma(dk, dk, -mu), dk * lane_val(ereg, lo));
     }
-    // one implicit-shift sweep, bulge chased from lo to hi
-    double dk = lane_val(dreg, lo), ek = lane_val(ereg, lo);
-    double y = dk * dk - mu;
-    double z = dk * ek;
-    double bulge = 0.0, eprev = 0.0;
-    double qk = lane < ms ? Q[lane + lo * kLd] : 0.0;
-    double wk = lane < m ? W[lane + lo * kLd] : 0.0;
-    for (int k = lo; k < hi; ++k) {
-      // next columns of Q and W (independent of the Givens chain)
-      const double qk1 = lane < ms ? Q[lane + (k + 1) * kLd] : 0.0;
-      const double wk1 = lane < m ? W[lane + (k + 1) * kLd] : 0.0;
-      const double dk1 = lane_val(dreg, k + 1);
-      const double ek1 = (k < hi - 1) ? lane_val(ereg, k + 1) : 0.0;
-      if (k > lo) {
-        y = eprev;
-        z = bulge;
-      }
-      double c, sn, r;
-      givens(y, z, c, sn, r);
-      if (k > lo && lane == k - 1) ereg = r;
-      const double ndk = c * dk + sn * ek;
-      const double nek = -sn * dk + c * ek;
-      bulge = sn * dk1;
-      const double ndk1 = c * dk1;
-      {
-        const double a = c * qk + sn * qk1, b = -sn * qk + c * qk1;
-        if (lane < ms) Q[lane + k * kLd] = a;
-        qk = b;
-      }
-      givens(ndk, bulge, c, sn, r);
-      if (lane == k) dreg = r;
-      eprev = c * nek + sn * ndk1;  // e_k
-      dk = -sn * nek + c * ndk1;    // d_{k+1}
-      ek = ek1;
-      if (k < hi - 1) {
-        bulge = sn * ek1;
-        ek = c * ek1;  // e_{k+1}
-      }
-      {
-        const double a = c * wk + sn * wk1, b = -sn * wk + c * wk1;
-        if (lane < m) W[lane + k * kLd] = a;
-        wk = b;
-      }
+    if (lane == 0) {
+      S.lo = lo;
+      S.hi = go ? hi : 0;
     }
-    if (lane == hi - 1) ereg = eprev;
-    if (lane == hi) dreg = dk;
-    if (lane < ms) Q[lane + hi * kLd] = qk;
-    if (lane < m) W[lane + hi * kLd] = wk;
-    nrot_q += hi - lo;
-    nrot_w += hi - lo;
+    __syncthreads();
+    if (pending && row) leaf_apply<ML>(S, S.sw[par ^ 1], plo, phi, lane);
+    pending = false;
+    if (!go) break;
+    __syncthreads();
   }
 
   // signs, ranks (ascending, ties by index) and output
-  __syncthreads();
   double sv = 0.0;
   int rank = 0;
   if (lane < m) {
@@ -271,7 +379,7 @@ __global__ __launch_bounds__(64) void k_leaf(const LeafDesc* __restrict__ leaves
     const double sj = fabs(lane_val(dreg, j));
     rank += (lane < m && (sj < sv || (sj == sv && j < lane))) ? 1 : 0;
   }
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();
   double* Uw = w.Uw + L.mat_off;
   double* Vw = w.Vw + L.mat_off;
   for (int c = 0; c < m; ++c) {
@@ -321,10 +429,10 @@ void launch_reset(Ctl* ctl, NodeState* nst, SecCount* sec, int nnodes, hipStream
 
 void launch_leaf(const LeafDesc* leaves, int nleaves, int max_m, const Work& w, hipStream_t st) {
   if (nleaves <= 0) return;
-  if (max_m <= 8) hipLaunchKernelGGL(k_leaf<8>, dim3(nleaves), dim3(64), 0, st, leaves, w);
-  else if (max_m <= 16) hipLaunchKernelGGL(k_leaf<16>, dim3(nleaves), dim3(64), 0, st, leaves, w);
-  else if (max_m <= 24) hipLaunchKernelGGL(k_leaf<24>, dim3(nleaves), dim3(64), 0, st, leaves, w);
-  else hipLaunchKernelGGL(k_leaf<kMaxLeaf>, dim3(nleaves), dim3(64), 0, st, leaves, w);
+  if (max_m <= 8) hipLaunchKernelGGL(k_leaf<8>, dim3(nleaves), dim3(128), 0, st, leaves, w);
+  else if (max_m <= 16) hipLaunchKernelGGL(k_leaf<16>, dim3(nleaves), dim3(128), 0, st, leaves, w);
+  else if (max_m <= 24) hipLaunchKernelGGL(k_leaf<24>, dim3(nleaves), dim3(128), 0, st, leaves, w);
+  else hipLaunchKernelGGL(k_leaf<kMaxLeaf>, dim3(nleaves), dim3(128), 0, st, leaves, w);
 }
 
 }  // namespace bdc

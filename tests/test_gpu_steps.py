@@ -51,6 +51,27 @@ def test_leaf_matches_oracle(solver, m, s):
     assert np.max(np.abs(Q.T @ Q - np.eye(m + s))) <= 1e-14
 
 
+@pytest.mark.parametrize("s", [0, 1])
+@pytest.mark.parametrize("m", [4, 7, 9, 16, 24, 25])
+def test_leaf_lds_classes(solver, m, s):
+    """The edges of the kernel's LDS sizes (8, 16, 24, 32 rows); the blocks
+    are split by zero superdiagonals so that sweeps of every length run."""
+    for cut in (0, m // 3, m - 2):
+        g = np.random.default_rng(100 * m + 10 * s + cut)
+        d = g.standard_normal(m)
+        e = g.standard_normal(m - 1 + s)
+        e[cut] = 0.0
+        sig, W, Q = (x.cpu().numpy() for x in solver.step_leaf(d, e, s))
+        ref, _, _, _ = oracle.leaf_svd(d, e, s)
+        B = obdc.dense_bidiagonal(d, e, s)
+        S = np.zeros((m, m + s))
+        S[np.arange(m), np.arange(m)] = sig
+        assert np.max(np.abs(sig - ref)) <= 1e-14 * ref[-1]
+        assert np.linalg.norm(B - W @ S @ Q.T) <= 1e-14 * np.linalg.norm(B)
+        assert np.max(np.abs(W.T @ W - np.eye(m))) <= 1e-14
+        assert np.max(np.abs(Q.T @ Q - np.eye(m + s))) <= 1e-14
+
+
 @pytest.mark.parametrize("case", ["zero_diag_mid", "zero_diag_last", "zero_e", "all_zero", "graded", "huge", "tiny"])
 def test_leaf_special(solver, case):
     m, s = 20, 1
