@@ -24,6 +24,7 @@
 
 #include "bdc_internal.h"
 #include "block_util.h"
+#include "gemm128.h"
 
 namespace bdc {
 namespace {
@@ -356,103 +357,6 @@ __device__ inline void gemm_tile(TileSmem<TM, TN>& sm, const double* __restrict_
   }
 }
 
-// Second form of the 128 x 128 tile: both 16-deep slabs double-buffered in
-// LDS (one barrier per slab: the next slab's global loads are issued before
-// the current slab's products and land in the other buffer after them), and
-// laid out so that neither the stores nor the operand reads conflict on the
-// LDS banks: A as [k][m] with a row stride of 144 doubles (the two k rows of
-// a half-wavefront's read are 32 banks apart), B as [n][k] with a column
-// stride of 17 doubles (k contiguous as in memory; the 16 columns of a read
-// fall on distinct banks).  70 KB of LDS; one workgroup per CU (the 64
-// accumulators per lane need more registers than two would leave).
-constexpr int kSA2 = 144, kSB2 = 17;
-struct TileSmem2 {
-  double A[2][TK * kSA2];
-  double B[2][128 * kSB2];
-};
-
-template <class Store>
-__device__ inline void gemm_tile2(TileSmem2& sm, const double* __restrict__ A, int64_t lda,
-                                  const double* __restrict__ B, int64_t ldb, int M, int N, int K, int tm0, int tn0,
-                                  Store store) {
-  constexpr int TM = 128, TN = 128;
-  constexpr int FA = TM * TK / kBlock, FB = TN * TK / kBlock;
-  const int t = threadIdx.x, wv = t >> 6, l = t & 63;
-  const int wm = wv & 1, wn = wv >> 1;
-  const int li = l & 15, lk = l >> 4;
-  v4d acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-  double ra[FA], rb[FB];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < FA; ++q) {
-      const int e = t + kBlock * q;
-      const int r = e % TM, kk = e / TM;
-      const int gr = tm0 + r, gk = k0 + kk;
-      ra[q] = (gr < M && gk < K) ? A[gr + (int64_t)gk * lda] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < FB; ++q) {
-      const int e = t + kBlock * q;
-      const int kk = e % TK, c = e / TK;
-      const int gk = k0 + kk, gc = tn0 + c;
-      rb[q] = (gk < K && gc < N) ? B[gk + (int64_t)gc * ldb] : 0.0;
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < FA; ++q) {
-      const int e = t + kBlock * q;
-      sm.A[buf][(e / TM) * kSA2 + e % TM] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < FB; ++q) {
-      const int e = t + kBlock * q;
-      sm.B[buf][(e / TK) * kSB2 + e % TK] = rb[q];
-    }
-  };
-  const int nslab = (K + TK - 1) / TK;
-  __syncthreads();  // the previous tile's readers are done with both buffers
-  load(0);
-  stash(0);
-  __syncthreads();
-  for (int sl = 0; sl < nslab; ++sl) {
-    const int buf = sl & 1;
-    if (sl + 1 < nslab) load((sl + 1) * TK);
-#pragma unroll
-    for (int kk = 0; kk < TK; kk += 4) {
-      double af[4], bf[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) af[a] = sm.A[buf][(kk + lk) * kSA2 + wm * 64 + a * 16 + li];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) bf[b] = sm.B[buf][(wn * 64 + b * 16 + li) * kSB2 + kk + lk];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
-    }
-    if (sl + 1 < nslab) {
-      stash(buf ^ 1);
-      __syncthreads();
-    }
-  }
-  // D[i][j] of a 16x16 block sits in lane j + 16 * (i % 4), register i / 4
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = tm0 + wm * 64 + a * 16 + lk + 4 * r;
-        const int colc = tn0 + wn * 64 + b * 16 + li;
-        if (row < M && colc < N) *(store.col(colc) + row) = acc[a][b][r];
-      }
-}
-
 // destination of output column c (row 0): the kept value's physical column
 struct NodeStore {
   double* C;
@@ -460,6 +364,7 @@ struct NodeStore {
   int64_t ld;
   int rowbase;
   __device__ double* col(int c) const { return C + rowbase + (int64_t)scol[c] * ld; }
+  __device__ void operator()(int r, int c, double v) const { col(c)[r] = v; }
 };
 
 // Nodes whose kept size N is at most w.small_n use 64 x 64 tiles, larger ones
@@ -511,8 +416,8 @@ __global__ __launch_bounds__(256, update_waves_per_eu(TM)) void k_update(const N
 }
 
 // The 128 x 128 class with the double-buffered tile (two workgroups per CU).
-__global__ __launch_bounds__(256, 1) void k_update2(const NodeDesc* __restrict__ nodes, Work w) {
-  __shared__ TileSmem2 sm;
+__global__ __launch_bounds__(256, 2) void k_update2(const NodeDesc* __restrict__ nodes, Work w) {
+  __shared__ Gemm128Lds sm;
   const NodeDesc nd = nodes[blockIdx.x];
   const NodeState st = w.st[nd.id];
   const int N = st.N, n1 = st.n1, n2 = st.n2;
@@ -533,9 +438,12 @@ __global__ __launch_bounds__(256, 1) void k_update2(const NodeDesc* __restrict__
   const double* B = Mv + (r0 + kb) + (int64_t)r0 * ld;
   NodeStore store{(isV ? w.Vw : w.Uw) + nd.mat_off, w.scol + vo, ld, r0 + rowoff};
   const int tiles_m = (rows + 127) / 128, tiles_n = (N + 127) / 128;
+  // workgroups y and y + P of a node share an XCD (gridDim.y is a multiple of P)
+  const int P = 8 / min(8, gridDim.x & -gridDim.x);
   for (int tile = blockIdx.y; tile < tiles_m * tiles_n; tile += gridDim.y) {
-    const int tm = tile % tiles_m, tn = tile / tiles_m;
-    gemm_tile2(sm, A, ld, B, ld, rows, N, K, tm * 128, tn * 128, store);
+    int tm, tn;
+    gemm128_place(tile, P, tiles_m, tiles_n, tm, tn);
+    gemm128_tile<false>(sm, A, ld, B, ld, rows, N, 0, K, tm * 128, tn * 128, store);
   }
 }
 
@@ -706,6 +614,7 @@ struct PlainStore {
   double* C;
   int64_t ldc;
   __device__ double* col(int c) const { return C + (int64_t)c * ldc; }
+  __device__ void operator()(int r, int c, double v) const { col(c)[r] = v; }
 };
 
 template <int TM, int TN>
@@ -719,13 +628,14 @@ __global__ __launch_bounds__(256) void k_gemm_plain(int M, int N, int K, const d
   }
 }
 
-__global__ __launch_bounds__(256, 1) void k_gemm_plain2(int M, int N, int K, const double* A, int lda,
+__global__ __launch_bounds__(256, 2) void k_gemm_plain2(int M, int N, int K, const double* A, int lda,
                                                         const double* B, int ldb, double* C, int ldc) {
-  __shared__ TileSmem2 sm;
+  __shared__ Gemm128Lds sm;
   const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
   for (int tile = blockIdx.x; tile < tiles_m * tiles_n; tile += gridDim.x) {
-    const int tm = tile % tiles_m, tn = tile / tiles_m;
-    gemm_tile2(sm, A, lda, B, ldb, M, N, K, tm * 128, tn * 128, PlainStore{C, ldc});
+    int tm, tn;
+    gemm128_place(tile, 8, tiles_m, tiles_n, tm, tn);
+    gemm128_tile<false>(sm, A, lda, B, ldb, M, N, 0, K, tm * 128, tn * 128, PlainStore{C, ldc});
   }
 }
 
@@ -1105,7 +1015,7 @@ void launch_update(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, 
     const int tiles = ((max_m + 1 + 127) / 128) * ((max_m + 127) / 128);
     const int gy = grid_y(nnodes, tiles, tu.grid128 * 2);
     if (tu.tile128)
-      hipLaunchKernelGGL(k_update2, dim3(nnodes, gy, 4), dim3(kBlock), 0, st, nodes, w);
+      hipLaunchKernelGGL(k_update2, dim3(nnodes, (gy + 7) & ~7, 4), dim3(kBlock), 0, st, nodes, w);
     else
       hipLaunchKernelGGL((k_update<128, 128>), dim3(nnodes, gy, 4), dim3(kBlock), 0, st, nodes, w);
   }
@@ -1114,18 +1024,24 @@ void launch_update(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, 
 void launch_gemm_plain(int M, int N, int K, const double* A, int lda, const double* B, int ldb,
                        double* C, int ldc, int tile128, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
-  if (N <= 96) {
-    int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles > 4096) tiles = 4096;
+  // 128 x 128 tiles (two workgroups per CU) once there are about as many as
+  // keep half the CUs busy, 64 x 64 tiles below that and for at most 64
+  // columns: 1000 x 1000 x 1000 (64 large tiles) 12.5 TFLOP/s with the large
+  // ones and 20.6 with the small, 2000 rows (128) 24.5 and 27.1, 2500 (160)
+  // 31.1 and 25.0, 4000 (256) 48.2 and 29.9; 20000 x 96 x 1000 24.4 and 20.3.
+  // 20000 x 1000 x 1000: 57 TFLOP/s, 8192 x 8192 x 8192: 67 (46.8 and 50 with
+  // one workgroup per CU and element loads with tests; a loop of products
+  // alone, no loads, reaches 72).
+  const int tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
+  if (N <= 64 || tiles128 < 144) {
+    const int tiles = std::min(4096, ((M + 63) / 64) * ((N + 63) / 64));
     hipLaunchKernelGGL((k_gemm_plain<64, 64>), dim3(tiles), dim3(kBlock), 0, st, M, N, K, A, lda, B, ldb, C, ldc);
+  } else if (tile128) {
+    hipLaunchKernelGGL(k_gemm_plain2, dim3(std::min(tiles128, 4096)), dim3(kBlock), 0, st, M, N, K, A, lda, B, ldb, C,
+                       ldc);
   } else {
-    int tiles = ((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles > 4096) tiles = 4096;
-    if (tile128)
-      hipLaunchKernelGGL(k_gemm_plain2, dim3(tiles), dim3(kBlock), 0, st, M, N, K, A, lda, B, ldb, C, ldc);
-    else
-      hipLaunchKernelGGL((k_gemm_plain<128, 128>), dim3(tiles), dim3(kBlock), 0, st, M, N, K, A, lda, B, ldb, C,
-                         ldc);
+    hipLaunchKernelGGL((k_gemm_plain<128, 128>), dim3(std::min(tiles128, 4096)), dim3(kBlock), 0, st, M, N, K, A, lda,
+                       B, ldb, C, ldc);
   }
 }
 

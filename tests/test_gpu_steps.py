@@ -31,6 +31,30 @@ def test_gemm_matches_numpy(solver, M, N, K):
     assert np.all(np.abs(C - ref) <= 4 * K * 2.0 ** -53 * scale + 1e-300)
 
 
+@pytest.mark.parametrize("M,N,K", [(18435, 70, 1), (18432, 128, 16), (18561, 65, 47), (9217, 257, 40), (18434, 66, 15)])
+def test_gemm_large_tile_edges(solver, M, N, K):
+    """The 128 x 128 tile at its edges (one row or column past a tile, K below,
+    at and past a slab), on views at odd offsets inside NaN: every element of
+    the result is a product of the operands' own entries."""
+    import torch
+    g = np.random.default_rng(M + N + K)
+
+    def inside_nan(X):
+        big = torch.full((X.shape[1] + 2, X.shape[0] + 3), float("nan"), dtype=torch.float64, device="cuda")
+        view = big[1:-1, 1:-2].T
+        view.copy_(torch.from_numpy(X))
+        return big, view
+
+    A, B = g.standard_normal((M, K)), g.standard_normal((K, N))
+    _, Ad = inside_nan(A)
+    _, Bd = inside_nan(B)
+    Cbig, Cd = inside_nan(np.zeros((M, N)))
+    solver.gemm(Ad, Bd, Cd)
+    ref, scale = A @ B, np.abs(A) @ np.abs(B)
+    assert np.all(np.abs(Cd.cpu().numpy() - ref) <= 4 * K * 2.0 ** -53 * scale + 1e-300)
+    assert int(torch.isnan(Cbig).sum()) == Cbig.numel() - M * N
+
+
 # ---------------------------------------------------------------- leaf
 @pytest.mark.parametrize("m", [1, 2, 3, 8, 17, 31, 32])
 @pytest.mark.parametrize("s", [0, 1])
