@@ -262,8 +262,9 @@ int bdc_step_gemm(bdc_handle_t handle, int M, int N, int K, const double* A, int
  * reflectors y_rs = 1, y_cs = ld; row-stored ones y_rs = ld, y_cs = 1, with
  * offset 1 for gebrd's row reflectors); tau[i] = 0 makes H_i the identity.
  * All pointers are device pointers; Y and tau are not written.  The
- * reflectors are applied `block` at a time (1..64; 0 = 64) in the modified
- * compact WY form of eq. inv_t / larft_update: T^{-1} = Y^T Y above its
+ * reflectors are applied `block` at a time (1..64; 0 = 64, of which up to
+ * eight blocks go together, or one where a workspace cap holds no more) in
+ * the modified compact WY form of eq. inv_t / larft_update: T^{-1} = Y^T Y above its
  * diagonal and 1/tau_i on it (gemm), Z = Y^T C (gemm), Z = T^{-1} \ Z (trsm),
  * C = C - Y Z (gemm), on the FP64 matrix cores.  Scratch is owned by the
  * handle (grown on demand).  Enqueues on `stream`; returns BDC_OK, -i for an
@@ -276,7 +277,8 @@ int bdc_apply_reflectors(bdc_handle_t handle, int trans, int m, int p, int k, in
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same arguments, kernels and results (bit for bit), but the
  * scratch is a fixed 32 MiB array of device memory per GPU, held until the
- * process ends, and C is transformed in panels of at most 512 columns.  No
+ * process ends, and C is transformed in panels of at most 512 columns and, where
+ * the scratch asks for it, in chunks of its rows.  No
  * hipMalloc, hipFree or allocating library call is made.  Limit:
  * 8 (m b + b^2 + 33 b max(b, min(p, 512))) + 1024 <= 32 MiB for the block
  * size b (m <= 48574 with b = 64 and p >= 512, any k); larger problems return

@@ -854,7 +854,7 @@ int reflector_args(bdc_handle_t h, int trans, int m, int p, int k, int offset, c
 
 namespace {
 // the handle's back-transformation scratch, grown to at least `bytes`
-int ensure_bt(bdc_handle_t h, size_t bytes) {
+int grow_bt(bdc_handle_t h, size_t bytes) {
   if (h->bt_bytes >= bytes) return BDC_OK;
   if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
   if (h->bt_arena) (void)hipFree(h->bt_arena);
@@ -868,6 +868,15 @@ int ensure_bt(bdc_handle_t h, size_t bytes) {
   h->bt_bytes = bytes;
   return BDC_OK;
 }
+
+// scratch and plan for m rows and p columns; where the memory for large
+// groups is not to be had, one group per block with the rows in chunks
+int ensure_bt(bdc_handle_t h, int m, int p, int block, int group, BtPlan* plan) {
+  *plan = backtr_plan(m, p, p, backtr_group(block, group), false);
+  if (grow_bt(h, plan->bytes) == BDC_OK) return BDC_OK;
+  *plan = backtr_plan(m, p, p, block, true);
+  return grow_bt(h, plan->bytes);
+}
 }  // namespace
 
 int bdc_apply_reflectors(bdc_handle_t h, int trans, int m, int p, int k, int offset, const double* Y, int64_t y_rs,
@@ -876,10 +885,11 @@ int bdc_apply_reflectors(bdc_handle_t h, int trans, int m, int p, int k, int off
   if (a != BDC_OK) return a == 1 ? BDC_OK : a;
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
-  const int rc = ensure_bt(h, backtr_bytes(m, p, block));
+  BtPlan plan;
+  const int rc = ensure_bt(h, m, p, block, kBtMaxGroup, &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
-  launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, block, h->bt_arena, p, st);
+  launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, plan, h->bt_arena, st);
   if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
   h->have_call = true;
@@ -892,12 +902,14 @@ int bdc_apply_reflectors_noalloc(bdc_handle_t h, int trans, int m, int p, int k,
   const int a = reflector_args(h, trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, &block);
   if (a != BDC_OK) return a == 1 ? BDC_OK : a;
   const int panel = std::min(p, kBtFixedPanel);
-  if (backtr_bytes(m, panel, block) > kBtFixedScratchBytes) return BDC_ERR_TOO_LARGE;
+  if (backtr_limit_bytes(m, panel, block) > kBtFixedScratchBytes) return BDC_ERR_TOO_LARGE;
+  const BtPlan plan = backtr_plan(m, p, std::min(p, kBtFixedWidth), backtr_group(block, kBtMaxGroup), true);
+  if (plan.bytes > kBtFixedScratchBytes) return BDC_ERR_TOO_LARGE;
   if (!h->bt_fixed) return BDC_ERR_HIP;  // the scratch address was not found at bdc_create
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   hipStream_t st = (hipStream_t)stream;
-  launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, block, h->bt_fixed, panel, st);
+  launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, plan, h->bt_fixed, st);
   if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
   h->have_call = true;
@@ -918,7 +930,8 @@ int bdc_geqrf(bdc_handle_t h, int m, int n, double* A, int lda, double* tau, int
   if (block < 1 || block > qr_max_block()) return -7;
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
-  int rc = ensure_bt(h, backtr_bytes(m, n, block));
+  BtPlan plan;
+  int rc = ensure_bt(h, m, n, block, kBtMaxBlock, &plan);
   if (rc != BDC_OK) return rc;
   const size_t sb = qr_sync_bytes(kQrMaxGrid);
   if (h->qr_sync_size < sb) {
@@ -933,7 +946,7 @@ int bdc_geqrf(bdc_handle_t h, int m, int n, double* A, int lda, double* tau, int
     h->qr_sync_size = sb;
   }
   hipStream_t st = (hipStream_t)stream;
-  rc = launch_geqrf(h->device, m, n, A, lda, tau, block, h->qr_sync, h->qr_sync_size, h->bt_arena, st);
+  rc = launch_geqrf(h->device, m, n, A, lda, tau, block, h->qr_sync, h->qr_sync_size, plan, h->bt_arena, st);
   if (rc != BDC_OK) return rc;
   if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
@@ -957,10 +970,13 @@ int bdc_orgqr(bdc_handle_t h, int m, int ncols, int k, const double* A, int lda,
   if (block < 1 || block > kBtMaxBlock) return -10;
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
-  const int rc = ensure_bt(h, backtr_bytes(m, ncols, block));
+  BtPlan plan;
+  // half the largest group: Q's leading columns, zero below their own group's
+  // pivots, are multiplied in full by every group before theirs
+  const int rc = ensure_bt(h, m, ncols, block, kBtMaxGroup / 2, &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
-  launch_orgqr(m, ncols, k, A, lda, tau, Q, ldq, block, h->bt_arena, st);
+  launch_orgqr(m, ncols, k, A, lda, tau, Q, ldq, plan, h->bt_arena, st);
   if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
   h->have_call = true;

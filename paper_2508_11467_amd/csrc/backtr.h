@@ -9,27 +9,38 @@
 namespace bdc {
 
 constexpr int kBtMaxBlock = 64;  // reflectors per block, at most
-constexpr int kBtSlices = 32;    // depth slices of the Y^T products, at most
+constexpr int kBtMaxGroup = 512; // reflectors applied together, at most (eight blocks of 64)
 
 // the allocation-free entry point: a fixed 32 MiB of device memory per GPU,
 // C taken in panels of at most 512 columns
 constexpr size_t kBtFixedScratchBytes = size_t(32) << 20;
 constexpr int kBtFixedPanel = 512;
+constexpr int kBtFixedWidth = 256;  // columns at a time within the fixed scratch
 constexpr int kBtMaxDevices = 64;
 
-// scratch bytes of launch_backtr for m rows, column panels of `panel`
-// columns and blocks of `block` reflectors
-size_t backtr_bytes(int m, int panel, int block);
+// Scratch of one back-transformation: offsets in doubles, all bytes.
+struct BtPlan {
+  int group, panel;  // reflectors applied together; columns of C at a time
+  bool fixed;        // rows in chunks whose scratch does not grow with m (the same sums)
+  int slices;        // depth slices of a chunk, at most (fixed)
+  size_t yp, p, pt, wsum, tsum, ti, di, z;
+  size_t bytes;
+};
+// bytes that bound the allocation-free entry point's problems, and that any
+// problem can be run in (group = block, fixed)
+size_t backtr_limit_bytes(int m, int panel, int block);
+// reflectors applied together for a block size
+inline int backtr_group(int block, int most) { return block == kBtMaxBlock ? most : block; }
+BtPlan backtr_plan(int m, int p, int panel, int group, bool fixed);
 
 // C (m x p, ldc) <- Q C (trans 0) or Q^T C (trans 1), Q = H_0 ... H_{k-1};
 // reflector i has its unit pivot at row i + offset, zeros above, and entry r
-// below at Y[r * rs + i * cs]; tau[i] = 0 makes H_i the identity.  The
-// columns of C are taken `panel` at a time (every column is transformed on
-// its own, so any panel width gives the same results).  The Y^T products
-// split their depth into at most kBtSlices slices (enough for about a
-// thousand workgroups over p columns), added in a fixed order.
+// below at Y[r * rs + i * cs]; tau[i] = 0 makes H_i the identity.  Groups of
+// plan.group reflectors from a plan made for at least m rows and p columns
+// (exactly p when its panel is narrower).  Panels and chunks give the same
+// results as one piece, bit for bit.
 void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, int64_t rs, int64_t cs,
-                   const double* tau, double* C, int ldc, int block, void* scratch, int panel, hipStream_t st);
+                   const double* tau, double* C, int ldc, const BtPlan& plan, void* scratch, hipStream_t st);
 
 // C (rows x N, ldc) -= Y (rows x K, ldy) Z (K x N, ldz), column-major, on the
 // FP64 matrix cores

@@ -51,21 +51,24 @@ __device__ inline void gemm128_place(int v, int P, int tiles_m, int tiles_n, int
   tn = in / h;
 }
 
-// C tile (tm0.., tn0..) of A (M x K) B (K x N) over k0 <= k < k1, all
-// column-major; element (r, k) of A at A[r + k lda], or at A[k + r lda] with
-// TRANSA.  store(row, col, value) for the tile's elements inside M x N.  Sums
-// run over k ascending in steps of four from k0.  256 threads.
-template <bool TRANSA, class Store>
+// C tile (tm0.., tn0.., TM x 128) of A (M x K) B (K x N) over k0 <= k < k1,
+// all column-major; element (r, k) of A at A[r + k lda], or at A[k + r lda]
+// with TRANSA.  store(row, col, value) for the tile's elements inside M x N.
+// Sums run over k ascending in steps of four from k0.  256 threads.  TM = 64
+// (a transposed A only) is for products of at most 64 rows.
+template <bool TRANSA, int TM = 128, class Store>
 __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A, int64_t lda,
                                     const double* __restrict__ B, int64_t ldb, int M, int N, int k0, int k1, int tm0,
                                     int tn0, const Store& store) {
   constexpr int TK = kG128K;
+  constexpr int BA = TM / 32;  // 16 x 16 blocks of a wavefront's rows; lines of a transposed A per thread
+  static_assert(TM == 128 || (TM == 64 && TRANSA), "tile");
   const int t = threadIdx.x, wv = t >> 6, l = t & 63;
   const int wm = wv & 1, wn = wv >> 1;
   const int li = l & 15, lk = l >> 4;
-  g128_acc acc[4][4];
+  g128_acc acc[BA][4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < BA; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = g128_acc{0.0, 0.0, 0.0, 0.0};
 
@@ -78,7 +81,7 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     offB[q] = (uint32_t)((min(line + 32 * q, N - 1 - tn0) * ldb + kp) * 8);
-    if (TRANSA) offA[q] = (uint32_t)((min(line + 32 * q, M - 1 - tm0) * lda + kp) * 8);
+    if (TRANSA && q < BA) offA[q] = (uint32_t)((min(line + 32 * q, M - 1 - tm0) * lda + kp) * 8);
   }
   if (!TRANSA) {
     const int r = min(2 * l, M - 2 - tm0);
@@ -89,10 +92,10 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
   const char* const baseA = reinterpret_cast<const char*>(TRANSA ? A + (int64_t)tm0 * lda : A + tm0);
   const char* const baseB = reinterpret_cast<const char*>(B + (int64_t)tn0 * ldb);
 
-  g128_pair ra[4], rb[4];
+  g128_pair ra[BA], rb[4];
   auto load = [&](int kb) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < BA; ++q) {
       if (TRANSA) {
         ra[q] = *reinterpret_cast<const g128_pair*>(baseA + (int64_t)kb * 8 + offA[q]);
       } else {
@@ -109,7 +112,8 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int r = tm0 + (TRANSA ? line + 32 * q : 2 * l + h), ka = kb + (TRANSA ? kp + h : wv + 4 * q);
-        ra[q][h] = (r < M && ka < k1) ? (TRANSA ? A[ka + (int64_t)r * lda] : A[r + (int64_t)ka * lda]) : 0.0;
+        if (q < BA)
+          ra[q][h] = (r < M && ka < k1) ? (TRANSA ? A[ka + (int64_t)r * lda] : A[r + (int64_t)ka * lda]) : 0.0;
         const int c = tn0 + line + 32 * q, kc = kb + kp + h;
         rb[q][h] = (c < N && kc < k1) ? B[kc + (int64_t)c * ldb] : 0.0;
       }
@@ -119,23 +123,24 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int ea = TRANSA ? (line + 32 * q) * kG128B + kp : (wv + 4 * q) * kG128A + 2 * l;
-      *reinterpret_cast<g128_pair16*>(&sm.A[buf][ea]) = g128_pair16{shifted ? ra[q].y : ra[q].x, ra[q].y};
+      if (q < BA)
+        *reinterpret_cast<g128_pair16*>(&sm.A[buf][ea]) = g128_pair16{shifted ? ra[q].y : ra[q].x, ra[q].y};
       *reinterpret_cast<g128_pair16*>(&sm.B[buf][(line + 32 * q) * kG128B + kp]) = g128_pair16{rb[q].x, rb[q].y};
     }
   };
   auto multiply = [&](int buf) {
 #pragma unroll
     for (int kk = 0; kk < TK; kk += 4) {
-      double af[4], bf[4];
+      double af[BA], bf[4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int row = wm * 64 + a * 16 + li;
+      for (int a = 0; a < BA; ++a) {
+        const int row = wm * (TM / 2) + a * 16 + li;
         af[a] = TRANSA ? sm.A[buf][row * kG128B + kk + lk] : sm.A[buf][(kk + lk) * kG128A + row];
       }
 #pragma unroll
       for (int b = 0; b < 4; ++b) bf[b] = sm.B[buf][(wn * 64 + b * 16 + li) * kG128B + kk + lk];
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < BA; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
@@ -168,12 +173,12 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
   }
   // D[i][j] of a 16x16 block sits in lane j + 16 * (i % 4), register i / 4
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < BA; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = tm0 + wm * 64 + a * 16 + lk + 4 * r;
+        const int row = tm0 + wm * (TM / 2) + a * 16 + lk + 4 * r;
         const int col = tn0 + wn * 64 + b * 16 + li;
         if (row < M && col < N) store(row, col, acc[a][b][r]);
       }

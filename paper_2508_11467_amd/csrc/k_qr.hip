@@ -267,7 +267,7 @@ int qr_panel_grid(int device, int rows_below, int b, int* grid, int* rows_per_wg
 }
 
 int launch_geqrf(int device, int m, int n, double* A, int lda, double* tau, int b, void* sync_buf, size_t sync_bytes,
-                 void* bt_scratch, hipStream_t st) {
+                 const BtPlan& plan, void* bt_scratch, hipStream_t st) {
   GridSync* sync = reinterpret_cast<GridSync*>(sync_buf);
   double* slots = reinterpret_cast<double*>(reinterpret_cast<char*>(sync_buf) + kGridSyncBytes);
   hipLaunchKernelGGL(k_qr_sync_init, dim3(1), dim3(256), 0, st, sync);
@@ -288,25 +288,26 @@ int launch_geqrf(int device, int m, int n, double* A, int lda, double* tau, int 
     const int nt = n - j0 - bw;
     if (nt > 0)
       launch_backtr(1, m - j0, nt, bw, 0, A + j0 + (int64_t)j0 * lda, 1, lda, tau + j0,
-                    A + j0 + (int64_t)(j0 + bw) * lda, lda, bw, bt_scratch, nt, st);
+                    A + j0 + (int64_t)(j0 + bw) * lda, lda, plan, bt_scratch, st);
   }
   return BDC_OK;
 }
 
-void launch_orgqr(int m, int ncols, int k, const double* A, int lda, const double* tau, double* Q, int ldq, int b,
-                  void* bt_scratch, hipStream_t st) {
+void launch_orgqr(int m, int ncols, int k, const double* A, int lda, const double* tau, double* Q, int ldq,
+                  const BtPlan& plan, void* bt_scratch, hipStream_t st) {
   const int64_t total = (int64_t)m * ncols;
   hipLaunchKernelGGL(k_qr_eye, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 65536)), dim3(256), 0, st, Q,
                      (int64_t)ldq, m, ncols);
   // blocks from the last to the first; block j acts on rows and columns from
   // its first pivot j b on (the columns before it are still those of the
   // identity, which its reflectors leave unchanged)
+  const int b = plan.group;
   const int nblk = (k + b - 1) / b;
   for (int q = nblk - 1; q >= 0; --q) {
     const int i0 = q * b, bw = std::min(b, k - i0);
     if (i0 >= m || i0 >= ncols) continue;
     launch_backtr(0, m - i0, ncols - i0, bw, 0, A + i0 + (int64_t)i0 * lda, 1, lda, tau + i0,
-                  Q + i0 + (int64_t)i0 * ldq, ldq, bw, bt_scratch, ncols - i0, st);
+                  Q + i0 + (int64_t)i0 * ldq, ldq, plan, bt_scratch, st);
   }
 }
 

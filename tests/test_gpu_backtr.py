@@ -127,3 +127,83 @@ def test_apply_reflectors_full_size_sampled(solver):
     err = float(np.max(np.abs(out - ref)))
     print(f"n=16384 back-transformation: max err on 6 columns {err:.2e}", flush=True)
     assert err <= 1e-12 * np.sqrt(n)
+
+
+@pytest.mark.parametrize("trans", [False, True])
+@pytest.mark.parametrize("m,p,k,offset,rows", [(1100, 130, 1100, 0, False), (1025, 300, 1024, 1, True),
+                                               (777, 33, 513, 0, False), (640, 129, 640, 5, True),
+                                               (90, 40, 150, 0, False)])
+def test_apply_reflectors_groups(solver, trans, m, p, k, offset, rows):
+    """Groups of several 64-blocks at their edges (a last group of one
+    reflector, a last block of one, reflectors past the last row), identities
+    among them whose stored entries are NaN, both storages: against the
+    oracle, and the allocation-free entry point bit for bit."""
+    import torch
+    g = np.random.default_rng(m + p + k)
+    Y = np.zeros((m, k))
+    tau = np.zeros(k)
+    for i in range(min(k, m - offset)):
+        v = g.standard_normal(m - offset - i - 1)
+        v *= 0.97 / max(np.linalg.norm(v), 1e-300)
+        Y[offset + i, i] = 1.0
+        Y[offset + i + 1:, i] = v
+        tau[i] = 2.0 / (1.0 + v @ v)
+    identities = [0, 70, min(k, m - offset) - 1]
+    tau[identities] = 0.0
+    stored = Y.copy()
+    stored[:, identities] = np.nan
+    Y[:, identities] = 0.0
+    C = g.standard_normal((m, p))
+    ref = hh.apply_q(Y, tau, C, trans=trans)
+    Yd = torch.from_numpy(np.ascontiguousarray(stored.T if rows else stored)).cuda()
+    td = torch.from_numpy(tau).cuda()
+    out = []
+    for noalloc in (False, True):
+        Cd = _colmajor(C)
+        solver.apply_reflectors(Yd, td, Cd, trans=trans, offset=offset, rows=rows, noalloc=noalloc)
+        out.append(Cd.cpu().numpy())
+    err = np.max(np.abs(out[0] - ref))
+    assert err <= 1e-13 * np.max(np.abs(C)) * np.sqrt(m), err
+    assert np.array_equal(out[0], out[1])
+
+
+def test_apply_reflectors_long_thin_chunks(solver):
+    """More rows than a chunk of the fixed scratch holds, few columns: both
+    entry points bit for bit, and Q^T (Q C) = C."""
+    import torch
+    m, p, k = 9001, 20, 130
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    Y = torch.tril(torch.randn((m, k), dtype=torch.float64, device="cuda", generator=gen), -1) * 0.01
+    tau = 2.0 / (1.0 + torch.sum(Y * Y, dim=0))
+    C = torch.randn((p, m), dtype=torch.float64, device="cuda", generator=gen).T
+    out = []
+    for noalloc in (False, True):
+        W = C.T.clone().T
+        solver.apply_reflectors(Y, tau, W, noalloc=noalloc)
+        out.append(W)
+    assert torch.equal(out[0], out[1])
+    solver.apply_reflectors(Y, tau, out[0], trans=True)
+    assert float(torch.max(torch.abs(out[0] - C))) <= 1e-13 * np.sqrt(m) * float(torch.max(torch.abs(C)))
+
+
+def test_apply_reflectors_under_a_workspace_cap(gpu):
+    """A cap that holds the scratch of one block at a time but not that of a
+    group still serves the call."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    m, p, k = 2000, 500, 700
+    cap = 8 * (m * 64 + 64 * 64 + 33 * 64 * p) + 1024
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    Y = torch.tril(torch.randn((m, k), dtype=torch.float64, device="cuda", generator=gen), -1) * 0.02
+    tau = 2.0 / (1.0 + torch.sum(Y * Y, dim=0))
+    C = torch.randn((p, m), dtype=torch.float64, device="cuda", generator=gen).T
+    out = []
+    for limit in (0, cap):
+        s = Solver(0, workspace_cap_bytes=limit)
+        W = C.T.clone().T
+        s.apply_reflectors(Y, tau, W)
+        out.append(W)
+        s.close()
+    assert float(torch.max(torch.abs(out[0] - out[1]))) <= 1e-13 * np.sqrt(m) * float(torch.max(torch.abs(C)))
