@@ -872,7 +872,7 @@ int grow_bt(bdc_handle_t h, size_t bytes) {
 // scratch and plan for m rows and p columns; where the memory for large
 // groups is not to be had, one group per block with the rows in chunks
 int ensure_bt(bdc_handle_t h, int m, int p, int block, int group, BtPlan* plan) {
-  *plan = backtr_plan(m, p, p, backtr_group(block, group), false);
+  *plan = backtr_plan(m, p, p, group, false);
   if (grow_bt(h, plan->bytes) == BDC_OK) return BDC_OK;
   *plan = backtr_plan(m, p, p, block, true);
   return grow_bt(h, plan->bytes);
@@ -886,7 +886,7 @@ int bdc_apply_reflectors(bdc_handle_t h, int trans, int m, int p, int k, int off
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  const int rc = ensure_bt(h, m, p, block, kBtMaxGroup, &plan);
+  const int rc = ensure_bt(h, m, p, block, backtr_group(block, kBtMaxGroup), &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, plan, h->bt_arena, st);
@@ -931,7 +931,7 @@ int bdc_geqrf(bdc_handle_t h, int m, int n, double* A, int lda, double* tau, int
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  int rc = ensure_bt(h, m, n, block, kBtMaxBlock, &plan);
+  int rc = ensure_bt(h, m, n, block, block, &plan);
   if (rc != BDC_OK) return rc;
   const size_t sb = qr_sync_bytes(kQrMaxGrid);
   if (h->qr_sync_size < sb) {
@@ -973,7 +973,7 @@ int bdc_orgqr(bdc_handle_t h, int m, int ncols, int k, const double* A, int lda,
   BtPlan plan;
   // half the largest group: Q's leading columns, zero below their own group's
   // pivots, are multiplied in full by every group before theirs
-  const int rc = ensure_bt(h, m, ncols, block, kBtMaxGroup / 2, &plan);
+  const int rc = ensure_bt(h, m, ncols, block, backtr_group(block, kBtMaxGroup / 2), &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_orgqr(m, ncols, k, A, lda, tau, Q, ldq, plan, h->bt_arena, st);

@@ -53,16 +53,17 @@ __device__ inline void gemm128_place(int v, int P, int tiles_m, int tiles_n, int
 
 // C tile (tm0.., tn0.., TM x 128) of A (M x K) B (K x N) over k0 <= k < k1,
 // all column-major; element (r, k) of A at A[r + k lda], or at A[k + r lda]
-// with TRANSA.  store(row, col, value) for the tile's elements inside M x N.
+// with TRANSA.  store(row, col, value) for the tile's elements inside M x N, or,
+// with Store::kReads, store(row, col, store.at(row, col), value).
 // Sums run over k ascending in steps of four from k0.  256 threads.  TM = 64
-// (a transposed A only) is for products of at most 64 rows.
+// or 32 (a transposed A only) is for products of so few rows.
 template <bool TRANSA, int TM = 128, class Store>
 __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A, int64_t lda,
                                     const double* __restrict__ B, int64_t ldb, int M, int N, int k0, int k1, int tm0,
                                     int tn0, const Store& store) {
   constexpr int TK = kG128K;
   constexpr int BA = TM / 32;  // 16 x 16 blocks of a wavefront's rows; lines of a transposed A per thread
-  static_assert(TM == 128 || (TM == 64 && TRANSA), "tile");
+  static_assert(TM == 128 || ((TM == 64 || TM == 32) && TRANSA), "tile");
   const int t = threadIdx.x, wv = t >> 6, l = t & 63;
   const int wm = wv & 1, wn = wv >> 1;
   const int li = l & 15, lk = l >> 4;
@@ -143,7 +144,7 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
       for (int a = 0; a < BA; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[b], af[a], acc[a][b], 0, 0, 0);
     }
   };
   int kb = k0, buf = 0;
@@ -171,17 +172,34 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
     multiply(buf);
     buf ^= 1;
   }
-  // D[i][j] of a 16x16 block sits in lane j + 16 * (i % 4), register i / 4
+  // The products are taken as B^T A^T: D[i][j] of a 16x16 block sits in lane
+  // j + 16 * (i % 4), register i / 4, so with i the column and j the row a
+  // wavefront's access is 16 consecutive rows of four columns (whole 128-byte
+  // lines, where A B would give 32 bytes of sixteen).  What the stores replace
+  // is read a block row at a time, before any of its stores.
 #pragma unroll
-  for (int a = 0; a < BA; ++a)
+  for (int a = 0; a < BA; ++a) {
+    const int row = tm0 + wm * (TM / 2) + a * 16 + li, col0 = tn0 + wn * 64 + lk;
+    double old[4][4];
+    if constexpr (Store::kReads) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int col = col0 + b * 16 + 4 * r;
+          old[b][r] = row < M && col < N ? store.at(row, col) : 0.0;
+        }
+    }
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = tm0 + wm * (TM / 2) + a * 16 + lk + 4 * r;
-        const int col = tn0 + wn * 64 + b * 16 + li;
-        if (row < M && col < N) store(row, col, acc[a][b][r]);
+        const int col = col0 + b * 16 + 4 * r;
+        if (row >= M || col >= N) continue;
+        if constexpr (Store::kReads) store(row, col, old[b][r], acc[a][b][r]);
+        else store(row, col, acc[a][b][r]);
       }
+  }
 }
 
 }  // namespace bdc

@@ -18,10 +18,10 @@
 // that is the bound (and the update's epilogue with it), from K = 512 on the
 // matrix cores are.  Eight 64-blocks therefore go as one group, the
 // triangular solve by 64-row blocks with inverted diagonal blocks, on the
-// matrix cores too.  8192 x 8192 with 8192 reflectors: 23.4 ms (47 TFLOP/s)
-// with groups of 512, 26.5 with 256, and 69.9 with 64 and one thread per
-// column in the solve (113 us a block, whatever its size); 3001 x 3001: 2.4,
-// 3.0 and 11.3 ms.
+// matrix cores too.  8192 x 8192 with 8192 reflectors: 22.3 ms (49 TFLOP/s)
+// with groups of 512, 26 with 256, and 69.9 with 64 and one thread per
+// column in the solve (113 us a block, whatever its size); 3001 x 3001: 2.3,
+// 2.9 and 11.3 ms.
 #include <algorithm>
 #include <mutex>
 
@@ -38,14 +38,17 @@ constexpr int kSolveCols = 16; // columns of W per workgroup of the solve
 constexpr int kTSlice = 512;   // depth slice of Y^T Y
 
 struct PartStore {
+  static constexpr bool kReads = false;
   double* P;
   int64_t ld;
   __device__ void operator()(int r, int c, double v) const { P[r + (int64_t)c * ld] = v; }
 };
 struct SubStore {
+  static constexpr bool kReads = true;
   double* C;
   int64_t ld;
-  __device__ void operator()(int r, int c, double v) const { C[r + (int64_t)c * ld] -= v; }
+  __device__ double at(int r, int c) const { return C[r + (int64_t)c * ld]; }
+  __device__ void operator()(int r, int c, double old, double v) const { C[r + (int64_t)c * ld] = old - v; }
 };
 
 // Rows [q0, q1) (counted from the group's first pivot r0) of the group's
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(256, 2) void k_bt_update(const double* __restrict__
 }
 
 constexpr int kBtSliceRows = 4096;      // rows of a slice of W, at most
-constexpr int kBtSlices = 32;           // slices of W, at most (unless kBtSliceRows asks for more),
+constexpr int kBtSlices = 64;           // slices of W, at most (unless kBtSliceRows asks for more),
 constexpr size_t kBtSliceDoubles = size_t(32) << 20;  // and what they hold together (likewise)
 // the fixed scratch: rows of a chunk, what a chunk's slices of W may hold,
 // rows of a chunk of Y^T Y
@@ -404,7 +407,7 @@ void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, 
     // rows of a chunk: whole slices of W
     const int chunk = plan.fixed ? slice * std::min(kBtChunk / slice, plan.slices) : rows;
     const int nchunk = (rows + chunk - 1) / chunk;
-    const int tm = bw <= 64 ? 64 : 128, tr = (bw + tm - 1) / tm, tt = (bw + 127) / 128;
+    const int tm = bw <= 32 ? 32 : bw <= 64 ? 64 : 128, tr = (bw + tm - 1) / tm, tt = (bw + 127) / 128;
     auto pack = [&](int q0, int q1) {
       const int64_t tot = (int64_t)(q1 - q0) * bw;
       hipLaunchKernelGGL(k_bt_pack, dim3((unsigned)std::min<int64_t>((tot + 255) / 256, 4096)), dim3(256), 0, st, Y,
@@ -414,7 +417,9 @@ void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, 
     auto ytx = [&](const double* X, int pw, int cr, int nz, int nzt) {
       const int cblocks = ((pw + 127) / 128 + 7) / 8 * 8 * tr * nz;
       const dim3 grid(cblocks + tr * tt * nzt);
-      if (tm == 64)
+      if (tm == 32)
+        hipLaunchKernelGGL(k_bt_ytx<32>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);
+      else if (tm == 64)
         hipLaunchKernelGGL(k_bt_ytx<64>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);
       else
         hipLaunchKernelGGL(k_bt_ytx<128>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);

@@ -379,7 +379,7 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
     const double sj = fabs(lane_val(dreg, j));
     rank += (lane < m && (sj < sv || (sj == sv && j < lane))) ? 1 : 0;
   }
-  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   double* Uw = w.Uw + L.mat_off;
   double* Vw = w.Vw + L.mat_off;
   for (int c = 0; c < m; ++c) {

@@ -359,6 +359,7 @@ __device__ inline void gemm_tile(TileSmem<TM, TN>& sm, const double* __restrict_
 
 // destination of output column c (row 0): the kept value's physical column
 struct NodeStore {
+  static constexpr bool kReads = false;
   double* C;
   const int* scol;
   int64_t ld;
@@ -611,6 +612,7 @@ __global__ __launch_bounds__(256, update_waves_per_eu(TM)) void k_update_flat(co
 }
 
 struct PlainStore {
+  static constexpr bool kReads = false;
   double* C;
   int64_t ldc;
   __device__ double* col(int c) const { return C + (int64_t)c * ldc; }
@@ -1029,7 +1031,7 @@ void launch_gemm_plain(int M, int N, int K, const double* A, int lda, const doub
   // columns: 1000 x 1000 x 1000 (64 large tiles) 12.5 TFLOP/s with the large
   // ones and 20.6 with the small, 2000 rows (128) 24.5 and 27.1, 2500 (160)
   // 31.1 and 25.0, 4000 (256) 48.2 and 29.9; 20000 x 96 x 1000 24.4 and 20.3.
-  // 20000 x 1000 x 1000: 57 TFLOP/s, 8192 x 8192 x 8192: 67 (46.8 and 50 with
+  // 20000 x 1000 x 1000: 60 TFLOP/s, 8192 x 8192 x 8192: 67 (46.8 and 50 with
   // one workgroup per CU and element loads with tests; a loop of products
   // alone, no loads, reaches 72).
   const int tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
