@@ -8,24 +8,28 @@
 // Panel (b <= 64 columns, rows j0..m-1): one cooperative grid of G
 // workgroups.  Every workgroup keeps the panel's top b x b block (the rows of
 // its pivots) in LDS and updates it redundantly, and owns a contiguous slice
-// of the rows below it, also in LDS.  Column c of the panel:
-//   1. the reflector of x (Section 4.1): alpha = the pivot entry, sigma =
-//      ||x below the pivot||^2, beta = -sign(alpha) sqrt(alpha^2 + sigma),
-//      y = x / (alpha - beta) below the pivot, 1 at it, tau = 2 / y^T y with
-//      y^T y = 1 + sigma / (alpha - beta)^2 (tau = 0, the identity, when
-//      sigma = 0);
-//   2. one grid reduction: w = y^T X for the later columns (per-workgroup
-//      partial sums, added by every workgroup in the same order:
-//      deterministic), and the owned rows' sums of x^2 and y^2 of the next
-//      column, so its sigma after the update x <- x - y tau w follows as
-//      sum x^2 - 2 tau w sum x y + (tau w)^2 sum y^2 plus the top block's
-//      rows -- recomputed by a second grid reduction when that difference
-//      has cancelled by more than 7 bits;
-//   3. X -= tau y w^T on the owned rows and the top block.
-// One grid all-reduce per column (workgroups meet in groups of 16, each
-// group's sum formed once, in workgroup order); every wait is bounded (a
-// flag reports an expired wait and the kernel ends), and the launch is
-// cooperative, so all workgroups are resident.
+// of the rows below it, also in LDS.  The columns go in steps of up to 8,
+// because a grid all-reduce costs about 10 us whatever it carries:
+//   1. one all-reduce per step: M = X_s^T [X_s X_later] over the owned rows of
+//      all workgroups (per-workgroup partial sums added by every workgroup in
+//      the same order: deterministic);
+//   2. the step's reflectors from M and the top block alone (Section 4.1):
+//      alpha = the pivot entry, sigma = ||x below the pivot||^2, beta =
+//      -sign(alpha) sqrt(alpha^2 + sigma), y = x / (alpha - beta) below the
+//      pivot, 1 at it, tau = 2 / y^T y with y^T y = 1 + sigma / (alpha -
+//      beta)^2 (tau = 0, the identity, when sigma = 0); w = tau y^T X; then
+//      M of the columns after it follows from x <- x - y w as <x_i, x_k> -
+//      w_i <y, x_k> - w_k <y, x_i> + w_i w_k <y, y>.  A column whose sum of
+//      squares has cancelled by more than 3 bits so far ends the step before
+//      it: the next step's all-reduce forms it anew;
+//   3. the step's reflectors applied to the owned rows: each row's entries of
+//      the step's columns one reflector after the other, then the later
+//      columns together.
+// Panels of 32 columns of 20000 rows: 525 us with an all-reduce and three
+// passes over LDS per column, 135 us so (four all-reduces).
+// Every wait of the all-reduce is bounded (a flag reports an expired wait and
+// the kernel ends), and the launch is cooperative, so all workgroups are
+// resident.
 #include <algorithm>
 
 #include "bdc_internal.h"
@@ -40,48 +44,45 @@ namespace {
 constexpr int kQrMaxB = 64;         // panel width, at most
 constexpr int kQrBlock = 1024;      // threads of a panel workgroup (16 wavefronts)
 constexpr int kQrWaves = kQrBlock / 64;
-constexpr int kQrXCap = 160 * kQrMaxB;  // doubles of the owned rows: 10240 / b rows
+constexpr int kQrXCap = 160 * kQrMaxB;  // entries of the owned rows: 10240 / b rows
+constexpr int kQrStep = 8;          // columns per all-reduce, at most
+constexpr int kQrSums = 256;        // sums per all-reduce, at most
+constexpr double kQrKeep = 0x1p-3;  // a column of a step keeps this share of its sum of squares
+// row stride of the owned rows: odd from 16 columns on, so that a wavefront
+// with a row per lane spreads over the LDS banks
+__device__ __host__ constexpr int qr_stride(int b) { return b >= 16 ? (b | 1) : b; }
 struct PanelLds {
-  double T[kQrMaxB * kQrMaxB];  // top block, T[i * b + k] = A(j0 + i, j0 + k)
-  double X[kQrXCap];            // owned rows, X[r * b + k]
-  double w[kQrMaxB];
-  double tot[kQrMaxB + 2];
-  double red[kQrWaves * (kQrMaxB + 2)];
-  double sc[kQrWaves];
+  double X[kQrXCap + kQrXCap / 16];  // owned rows, X[r * stride + k]
+  double T[kQrMaxB * (kQrMaxB + 1)];  // top block, T[i * (b + 1) + k] = A(j0 + i, j0 + k)
+  double red[kQrWaves * kQrSums];
+  double M[kQrSums];                 // M[i * nk + k] = <x_{c+i}, x_{c+k}>
+  double W[kQrStep * kQrMaxB];       // W[i * 64 + k]: w of reflector i, column k of the panel
+  double P[kQrMaxB];                 // the top block's part of M's row i
+  double big[kQrStep];               // sum of the terms' sizes in M[i][i]
   unsigned sh[3];
 };
 
-// Sum over the workgroup of the wavefront partials of slot q, in wavefront
-// order
-__device__ __forceinline__ double red_waves(const double* red, int q) {
-  constexpr int S = kQrMaxB + 2;
-  double s = 0.0;
-#pragma unroll
-  for (int u = 0; u < kQrWaves; ++u) s += red[u * S + q];
-  return s;
+// sum over a wavefront, in lane 63 (row shifts, then the row totals)
+__device__ __forceinline__ double wave_sum_last(double x) {
+#define QR_DPP(ctrl, rows)                                                              \
+  x += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), ctrl, rows, 0xF, false), \
+                        __builtin_amdgcn_update_dpp(0, __double2loint(x), ctrl, rows, 0xF, false))
+  QR_DPP(0x111, 0xF);  // row_shr:1
+  QR_DPP(0x112, 0xF);  // row_shr:2
+  QR_DPP(0x114, 0xF);  // row_shr:4
+  QR_DPP(0x118, 0xF);  // row_shr:8
+  QR_DPP(0x142, 0xA);  // row_bcast:15 into rows 1 and 3
+  QR_DPP(0x143, 0xC);  // row_bcast:31 into rows 2 and 3
+#undef QR_DPP
+  return x;
 }
 
-// workgroup sum of one value per thread (every thread gets it), wavefronts
-// added in order
-__device__ inline double qr_block_sum(double v, double* sh) {
-  v = wave_sum(v);
-  const int wv = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[wv] = v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int u = 0; u < kQrWaves; ++u) s += sh[u];
-  return s;
-}
-
-// grid: G workgroups (cooperative), kQrBlock threads.  slots: 2 x G x (64 + 2)
-// doubles; gslots: 2 x grid_group_doubles(64 + 2).
+// grid: G workgroups (cooperative), kQrBlock threads.  slots: 2 x G x kQrSums
+// doubles; gslots: 2 x grid_group_doubles(kQrSums).
 __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A, int64_t lda, int m, int j0, int b,
                                                      int rows_per_wg, double* __restrict__ tau,
                                                      double* __restrict__ slots, double* __restrict__ gslots,
                                                      GridSync* sync) {
-  constexpr int S = kQrMaxB + 2;  // slot stride: w partials, then two sums
   __shared__ PanelLds L;
   const int t = threadIdx.x, G = gridDim.x, g = blockIdx.x;
   const int ln = t & 63, wv = t >> 6;
@@ -90,143 +91,170 @@ __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A
   const int r0 = below0 + g * rows_per_wg;         // owned rows [r0, r1)
   const int r1 = min(m, r0 + rows_per_wg);
   const int R = max(0, r1 - r0);
+  const int XS = qr_stride(b), TS = b + 1;
   double* Ap = A + j0 + (int64_t)j0 * lda;         // panel origin
   for (int e = t; e < top * b; e += kQrBlock) {
     const int i = e % top, k = e / top;
-    L.T[i * b + k] = Ap[i + (int64_t)k * lda];
+    L.T[i * TS + k] = Ap[i + (int64_t)k * lda];
   }
   for (int e = t; e < R * b; e += kQrBlock) {
     const int r = e % R, k = e / R;
-    L.X[r * b + k] = A[(r0 + r) + (int64_t)(j0 + k) * lda];
+    L.X[r * XS + k] = A[(r0 + r) + (int64_t)(j0 + k) * lda];
   }
   __syncthreads();
-  int phase = 0;  // slot buffer of the next reduction
-  // owned-row sum of squares of column c, reduced over the grid (exact)
-  auto owned_sq = [&](int c) -> double {
-    double* sl = slots + (size_t)phase * G * S;
-    double* gsl = gslots + (size_t)phase * grid_group_doubles(S);
-    phase ^= 1;
-    double s = 0.0;
-    for (int r = t; r < R; r += kQrBlock) s += L.X[r * b + c] * L.X[r * b + c];
-    s = qr_block_sum(s, L.sc);
-    if (t == 0) sl[(size_t)g * S] = s;
-    if (!grid_allreduce(sync, sl, gsl, S, 1, L.tot, L.red, L.sh)) return -1.0;
-    return L.tot[0];
-  };
-  // sigma of column 0: everything below its pivot
-  double own = owned_sq(0);
-  if (own < 0.0) return;
-  for (int c = 0; c < b; ++c) {
+  int phase = 0;  // slot buffer of the next all-reduce
+  for (int c = 0; c < b;) {
     if (c >= top) {  // no pivot row left: identities
-      if (g == 0 && t == 0) tau[j0 + c] = 0.0;
-      continue;
+      if (g == 0 && t < b - c) tau[j0 + c + t] = 0.0;
+      break;
     }
-    double tp = 0.0;  // top block rows below the pivot (identical on every workgroup)
-    for (int i = c + 1; i < top; ++i) tp += L.T[i * b + c] * L.T[i * b + c];
-    const double sigma = own + tp;
-    const double alpha = L.T[c * b + c];
-    double beta = alpha, tc = 0.0, scale = 0.0;
-    if (sigma > 0.0) {
-      const double nrm = sqrt(alpha * alpha + sigma);
-      beta = -copysign(nrm, alpha);
-      const double den = alpha - beta;
-      scale = 1.0 / den;
-      tc = 2.0 / (1.0 + sigma / (den * den));
-    }
-    // every wavefront has read the top block's column c (tp) before it is
-    // scaled
-    __syncthreads();
-    // y below the pivot: owned rows and the top block's rows c+1..
-    for (int r = t; r < R; r += kQrBlock) L.X[r * b + c] *= scale;
-    for (int i = c + 1 + t; i < top; i += kQrBlock) L.T[i * b + c] *= scale;
-    __syncthreads();
-    const int nk = b - c - 1;  // later columns
-    if (nk > 0) {
-      // one reduction: w_k = y^T X[:, k] (owned rows) for the later
-      // columns, and for the next column sum x^2 and sum y^2 (owned rows),
-      // from which its sigma after the update follows
-      double* sl = slots + (size_t)phase * G * S;
-      double* gsl = gslots + (size_t)phase * grid_group_doubles(S);
-      phase ^= 1;
-      const int k = c + 1 + ln;
-      double s = 0.0, sxx = 0.0, syy = 0.0;
-      for (int r = wv; r < R; r += kQrWaves) {
-        const double y = L.X[r * b + c];
-        if (k < b) s += y * L.X[r * b + k];
-        if (ln == 0) {
-          const double x = L.X[r * b + c + 1];
-          sxx += x * x;
-          syy += y * y;
+    const int nk = b - c;
+    const int s = min(min(kQrStep, top - c), kQrSums / nk);
+    // M's partial sums over the owned rows: lane -> column (two rows at a
+    // time where the columns leave half of the lanes), wavefronts over the rows
+    {
+      double acc[kQrStep] = {};
+      const bool two = nk <= 32;
+      const int k = two ? ln & 31 : ln, h = two ? ln >> 5 : 0;
+      if (k < nk) {
+        for (int r = two ? 2 * wv + h : wv; r < R; r += two ? 2 * kQrWaves : kQrWaves) {
+          const double* x = L.X + r * XS + c;
+          const double xk = x[k];
+#pragma unroll
+          for (int i = 0; i < kQrStep; ++i)
+            if (i < s) acc[i] = fma(x[i], xk, acc[i]);
         }
       }
-      L.red[wv * S + ln] = s;
-      if (ln == 0) {
-        L.red[wv * S + kQrMaxB] = sxx;
-        L.red[wv * S + kQrMaxB + 1] = syy;
-      }
-      __syncthreads();
-      // slot layout: w partials 0..nk-1, then sum x^2, sum y^2
-      if (t < nk) sl[(size_t)g * S + t] = red_waves(L.red, t);
-      if (t == 64) sl[(size_t)g * S + nk] = red_waves(L.red, kQrMaxB);
-      if (t == 65) sl[(size_t)g * S + nk + 1] = red_waves(L.red, kQrMaxB + 1);
-      if (!grid_allreduce(sync, sl, gsl, S, nk + 2, L.tot, L.red, L.sh)) return;
-      if (t < nk) {
-        const int kk = c + 1 + t;
-        const double tot = L.tot[t];
-        double tq = L.T[c * b + kk];  // pivot row, y = 1
-        for (int i = c + 1; i < top; ++i) tq += L.T[i * b + c] * L.T[i * b + kk];
-        L.w[t] = tc * (tot + tq);
-      }
-      if (t == 0) {
-        L.sc[1] = L.tot[0];       // owned rows' y^T x of the next column
-        L.sc[2] = L.tot[nk];      // sum x^2
-        L.sc[3] = L.tot[nk + 1];  // sum y^2
-      }
-      __syncthreads();
-      // the next column's owned-row sum of squares after x <- x - y a,
-      // a = tau w: sxx - 2 a sxy + a^2 syy
-      {
-        const double a = L.w[0], sxy = L.sc[1], sxx = L.sc[2], syy = L.sc[3];
-        const double big = sxx + a * a * syy;
-        own = (sxx - 2.0 * a * sxy) + a * a * syy;
-        // cancelled by more than 7 bits: recompute after the update (a
-        // decision every workgroup takes alike); big = 0 means the owned
-        // rows of the next column are zero before and after
-        if (big == 0.0) own = 0.0;
-        else if (!(own > 0x1p-7 * big)) own = -2.0;
-      }
-      // X -= y (tau w)^T on the owned rows and the top block's rows c..
-      for (int e = t; e < R * nk; e += kQrBlock) {
-        const int r = e / nk, kq = e - r * nk;
-        L.X[r * b + c + 1 + kq] -= L.X[r * b + c] * L.w[kq];
-      }
-      for (int e = t; e < (top - c) * nk; e += kQrBlock) {
-        const int i = c + e / nk, kq = e % nk;
-        const double y = i == c ? 1.0 : L.T[i * b + c];
-        L.T[i * b + c + 1 + kq] -= y * L.w[kq];
-      }
-      __syncthreads();
-      if (own == -2.0) {
-        own = owned_sq(c + 1);
-        if (own < 0.0) return;
-      }
-    }
-    // the pivot entry becomes R's diagonal
-    if (t == 0) {
-      L.T[c * b + c] = beta;
-      if (g == 0) tau[j0 + c] = tc;
+      double* part = L.red + wv * kQrSums + k;
+      if (h == 0 && k < nk)
+#pragma unroll
+        for (int i = 0; i < kQrStep; ++i)
+          if (i < s) part[i * nk] = acc[i];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (h == 1 && k < nk)
+#pragma unroll
+        for (int i = 0; i < kQrStep; ++i)
+          if (i < s) part[i * nk] += acc[i];
     }
     __syncthreads();
+    double* sl = slots + (size_t)phase * G * kQrSums;
+    double* gsl = gslots + (size_t)phase * grid_group_doubles(kQrSums);
+    phase ^= 1;
+    if (t < s * nk) {
+      double v = 0.0;
+#pragma unroll
+      for (int u = 0; u < kQrWaves; ++u) v += L.red[u * kQrSums + t];
+      sl[(size_t)g * kQrSums + t] = v;
+    }
+    if (!grid_allreduce(sync, sl, gsl, kQrSums, s * nk, L.M, L.red, L.sh)) return;
+    if (t < s) L.big[t] = L.M[t * nk + t];
+    // the step's reflectors
+    double sc[kQrStep];
+    int done = 0;
+#pragma unroll
+    for (int i = 0; i < kQrStep; ++i) {
+      sc[i] = 0.0;
+      if (i > done || i >= s) continue;  // the step has ended
+      const int j = c + i;
+      // the top block's part of row i of M (rows below the pivot), and the
+      // last pivot's column scaled now that nobody reads it unscaled
+      for (int k = j + wv; k < b; k += kQrWaves) {
+        const double v = ln > j && ln < top ? L.T[ln * TS + j] * L.T[ln * TS + k] : 0.0;
+        const double p = wave_sum_last(v);
+        if (ln == 63) L.P[k] = p;
+      }
+      if (i > 0 && t >= j && t < top) L.T[t * TS + j - 1] *= sc[i > 0 ? i - 1 : 0];
+      __syncthreads();
+      const double own = L.M[i * nk + i], big = L.big[i];
+      if (i > 0 && !(own > kQrKeep * big) && big != 0.0) continue;  // cancelled: a decision every workgroup takes alike
+      done = i + 1;
+      const double sigma = own + L.P[j], alpha = L.T[j * TS + j];
+      double beta = alpha, tc = 0.0;
+      if (sigma > 0.0) {
+        const double nrm = sqrt(alpha * alpha + sigma);
+        beta = -copysign(nrm, alpha);
+        const double den = alpha - beta;
+        sc[i] = 1.0 / den;
+        tc = 2.0 / (1.0 + sigma / (den * den));
+      }
+      if (t > i && t < nk)
+        L.W[i * kQrMaxB + c + t] = tc * (sc[i] * (L.M[i * nk + t] + L.P[c + t]) + L.T[j * TS + c + t]);
+      __syncthreads();
+      // the top block, and M of the step's later columns, after this reflector
+      for (int e = t; e < (top - j) * (nk - i - 1); e += kQrBlock) {
+        const int q = e / (nk - i - 1), r = j + q, k = j + 1 + e - q * (nk - i - 1);
+        const double y = q == 0 ? 1.0 : L.T[r * TS + j] * sc[i];
+        L.T[r * TS + k] -= y * L.W[i * kQrMaxB + k];
+      }
+      const int left = s - i - 1;
+      for (int e = t; e < left * nk; e += kQrBlock) {
+        const int u = i + 1 + e / nk, k = e - (e / nk) * nk;
+        if (k < u) continue;
+        const double wu = L.W[i * kQrMaxB + c + u], wk = L.W[i * kQrMaxB + c + k];
+        const double yu = sc[i] * L.M[i * nk + u], yk = sc[i] * L.M[i * nk + k], yy = sc[i] * (sc[i] * own);
+        L.M[u * nk + k] = L.M[u * nk + k] - wu * yk - wk * yu + wu * wk * yy;
+        if (k == u) L.big[u] += wu * wu * yy;
+      }
+      // the pivot entry becomes R's diagonal (row j's other entries are above)
+      if (t == 0) {
+        L.T[j * TS + j] = beta;
+        if (g == 0) tau[j0 + j] = tc;
+      }
+      __syncthreads();
+    }
+    // the last reflector's column of the top block (a column that ended the
+    // step early has scaled it already)
+#pragma unroll
+    for (int i = 0; i < kQrStep; ++i)
+      if (done == s && i == s - 1 && t > c + i && t < top) L.T[t * TS + c + i] *= sc[i];
+    // owned rows: the step's columns, a row per thread
+    for (int r = t; r < R; r += kQrBlock) {
+      double* xr = L.X + r * XS + c;
+      double x[kQrStep];
+#pragma unroll
+      for (int i = 0; i < kQrStep; ++i) x[i] = i < done ? xr[i] : 0.0;
+#pragma unroll
+      for (int i = 0; i < kQrStep; ++i) {
+        if (i >= done) break;
+        x[i] *= sc[i];
+#pragma unroll
+        for (int u = i + 1; u < kQrStep; ++u)
+          if (u < done) x[u] -= x[i] * L.W[i * kQrMaxB + c + u];
+        xr[i] = x[i];
+      }
+    }
+    __syncthreads();
+    // and the later ones
+    {
+      const int nl = nk - done;
+      const bool two = nl <= 32;
+      const int k = two ? ln & 31 : ln, h = two ? ln >> 5 : 0;
+      if (k < nl) {
+        double wk[kQrStep];
+#pragma unroll
+        for (int i = 0; i < kQrStep; ++i) wk[i] = i < done ? L.W[i * kQrMaxB + c + done + k] : 0.0;
+        for (int r = two ? 2 * wv + h : wv; r < R; r += two ? 2 * kQrWaves : kQrWaves) {
+          double* x = L.X + r * XS + c;
+          double v = x[done + k];
+#pragma unroll
+          for (int i = 0; i < kQrStep; ++i)
+            if (i < done) v -= x[i] * wk[i];
+          x[done + k] = v;
+        }
+      }
+    }
+    __syncthreads();
+    c += done;
   }
   // write back: owned rows, and the top block from workgroup 0
   for (int e = t; e < R * b; e += kQrBlock) {
     const int r = e % R, k = e / R;
-    A[(r0 + r) + (int64_t)(j0 + k) * lda] = L.X[r * b + k];
+    A[(r0 + r) + (int64_t)(j0 + k) * lda] = L.X[r * XS + k];
   }
   if (g == 0)
     for (int e = t; e < top * b; e += kQrBlock) {
       const int i = e % top, k = e / top;
-      Ap[i + (int64_t)k * lda] = L.T[i * b + k];
+      Ap[i + (int64_t)k * lda] = L.T[i * TS + k];
     }
 }
 
@@ -244,7 +272,7 @@ __global__ __launch_bounds__(256) void k_qr_eye(double* __restrict__ Q, int64_t 
 }  // namespace
 
 size_t qr_sync_bytes(int max_wg) {
-  return kGridSyncBytes + 2 * ((size_t)max_wg * (kQrMaxB + 2) + grid_group_doubles(kQrMaxB + 2)) * sizeof(double);
+  return kGridSyncBytes + 2 * ((size_t)max_wg * kQrSums + grid_group_doubles(kQrSums)) * sizeof(double);
 }
 
 int qr_max_block() { return kQrMaxB; }
@@ -279,7 +307,7 @@ int launch_geqrf(int device, int m, int n, double* A, int lda, double* tau, int 
     if (qr_panel_grid(device, rows_below, bw, &G, &R) != 0) return BDC_ERR_TOO_LARGE;
     if (qr_sync_bytes(G) > sync_bytes) return BDC_ERR_TOO_LARGE;
     int64_t lda64 = lda;
-    double* gslots = slots + 2 * (size_t)G * (kQrMaxB + 2);
+    double* gslots = slots + 2 * (size_t)G * kQrSums;
     void* args[] = {&A, &lda64, &m, &j0, const_cast<int*>(&bw), &R, &tau, &slots, &gslots, &sync};
     if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_qr_panel), dim3(G), dim3(kQrBlock), args, 0, st) !=
         hipSuccess)

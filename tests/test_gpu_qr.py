@@ -109,6 +109,42 @@ def test_geqrf_rank_deficient(solver):
     assert np.max(np.abs(Q.T @ Q - np.eye(n))) <= 1e-13
 
 
+@pytest.mark.parametrize("block", [1, 7, 8, 9, 31, 64])
+@pytest.mark.parametrize("m,n", [(500, 70), (70, 70), (12000, 40)])
+def test_geqrf_steps_of_columns(solver, m, n, block):
+    """Panels around the 8 columns of an all-reduce, and over several
+    workgroups: R, tau and the reflectors as the oracle's."""
+    g = np.random.default_rng(m + n + block)
+    A = g.standard_normal((m, n))
+    F, tau, Q = _gpu_qr(solver, A, block)
+    R0, Y0, tau0 = hh.qr(A)
+    scale = np.linalg.norm(A, 2)
+    assert np.max(np.abs(np.triu(F[:n]) - R0)) <= 1e-12 * scale
+    assert np.max(np.abs(tau - tau0)) <= 1e-12
+    assert np.max(np.abs(np.tril(F, -1) + np.eye(m, n) - Y0)) <= 1e-11
+    assert np.max(np.abs(Q.T @ Q - np.eye(n))) <= 1e-13 * max(1.0, np.sqrt(m / 100))
+
+
+@pytest.mark.parametrize("eps", [0.3, 1e-2, 1e-6, 1e-12])
+@pytest.mark.parametrize("m", [60, 400, 9000])
+def test_geqrf_nearly_dependent_columns(solver, m, eps):
+    """Columns that cancel almost wholly against the ones before them (every
+    one, every third, a pair of blocks): the factorisation holds to working
+    precision whatever the cancellation, A = QR and Q orthonormal."""
+    g = np.random.default_rng(m)
+    n = 48
+    for pattern in (lambda j: True, lambda j: j % 3 == 0, lambda j: j in (7, 8, 16)):
+        A = g.standard_normal((m, n))
+        for j in range(1, n):
+            if pattern(j):
+                A[:, j] = A[:, j - 1] * 0.5 + eps * A[:, j]
+        F, tau, Q = _gpu_qr(solver, A, 0)
+        R = np.triu(F[:n])
+        assert np.linalg.norm(Q @ R - A) <= 1e-14 * np.sqrt(m) * np.linalg.norm(A)
+        assert np.max(np.abs(Q.T @ Q - np.eye(n))) <= 1e-13 * max(1.0, np.sqrt(m / 100))
+        assert np.all((tau >= 0.0) & (tau <= 2.0 + 1e-15))
+
+
 def test_geqrf_rejects_more_rows_than_the_resident_grid(solver):
     """A panel whose rows below its top block exceed 160 per workgroup of the
     resident grid is refused on the host before any work is enqueued."""
