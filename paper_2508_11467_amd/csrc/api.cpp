@@ -83,7 +83,8 @@ struct bdc_handle_s {
   bool plan_valid = false;
   hipStream_t last_stream = nullptr;
   bool have_call = false;
-  // captured launch sequence of the current plan and buffers
+  // captured launch sequence of the current plan (all of a call but its first
+  // launch, which hands over the buffers)
   hipStream_t cap_stream = nullptr;
   // second stream of the captured sequence (each level's rotations and
   // gather beside its secular solve, Löwner z and vectors) and its fork and
@@ -91,7 +92,6 @@ struct bdc_handle_s {
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipGraphExec_t gexec = nullptr;
-  const void* gkey[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   struct Rec {
     int kind;
     hipEvent_t a, b;
@@ -143,7 +143,6 @@ bool valid(bdc_handle_t h) { return h != nullptr && h->magic == kMagic; }
 void drop_graph(bdc_handle_t h) {
   if (h->gexec) (void)hipGraphExecDestroy(h->gexec);
   h->gexec = nullptr;
-  for (auto& k : h->gkey) k = nullptr;
 }
 
 void free_plan(Plan& p) {
@@ -450,16 +449,12 @@ struct Timer {
   }
 };
 
-// side: a second stream for each level's rotations and gather, or null to
-// run every launch on st
-int run_plan(bdc_handle_t h, const double* d, const double* e, double* sigma, double* U, double* VT,
-             hipStream_t st, hipStream_t side = nullptr) {
+// Everything of a call after its first launch (start_call).  side: a second
+// stream for each level's rotations and gather, or null to run every launch on
+// st
+int run_plan(bdc_handle_t h, hipStream_t st, hipStream_t side = nullptr) {
   const Plan& p = h->plan;
   Work w = h->w;
-  w.d = d;
-  w.e = e;
-  w.GU = U;
-  w.GV = VT;
   w.max_secular_iters = h->opt.max_secular_iters;
   w.max_leaf_sweeps = h->opt.max_leaf_sweeps;
   w.learned_min_n = h->opt.learned_min_n;
@@ -475,10 +470,6 @@ int run_plan(bdc_handle_t h, const double* d, const double* e, double* sigma, do
   h->last_split_min_n = w.oz.min_n;
   w.small_n = h->tune.small_n;
   w.sec_small_n = h->tune.sec_small_n;
-  {
-    Timer t(h, st, kReset);
-    launch_reset(w.ctl, w.st, w.sec, p.nnodes, st);
-  }
   if (learned) {
     Timer t(h, st, kStart);
     launch_mlp_pack(h->mlp, h->mlp_pk, st);
@@ -524,10 +515,10 @@ int run_plan(bdc_handle_t h, const double* d, const double* e, double* sigma, do
     // a single problem whose size is a multiple of 8 chunks (4096) takes the
     // XCD-aligned 4 KB-chunk form
     if (np == 1 && p.sizes[0] % (8 * kFinalChunk) == 0)
-      launch_final_single(p.sizes[0], w, sigma, U, VT, st);
+      launch_final_single(p.sizes[0], w, st);
     else
       launch_final(p.dev_prob, p.dev_prob + np, p.dev_prob + 2 * np, p.dev_prob + 3 * np, p.dev_prob + 4 * np,
-                   p.dev_uprob, p.dev_vprob, p.total_cols, p.total_tiles, w, sigma, U, VT, st);
+                   p.dev_uprob, p.dev_vprob, p.total_cols, p.total_tiles, w, st);
   }
   if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
@@ -555,17 +546,24 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
   if (h->plan.total_n == 0) {
     h->last_stream = st;
     h->have_call = true;
-    launch_reset(h->w.ctl, h->w.st, h->w.sec, 0, st);
+    launch_reset(h->w.ctl, h->w.st, h->w.sec, 0, Io{}, st);
     return hipGetLastError() == hipSuccess ? BDC_OK : BDC_ERR_HIP;
   }
-  if (h->opt.timing || !h->opt.use_graph || h->harvest) return run_plan(h, d, e, sigma, U, VT, st);
-  // replay the captured sequence when the plan and the buffers are the same
-  const void* key[5] = {d, e, sigma, U, VT};
-  bool same = h->gexec != nullptr;
-  for (int i = 0; i < 5 && same; ++i) same = key[i] == h->gkey[i];
-  if (!same) {
+  auto start_call = [&] {
+    Timer t(h, st, kReset);
+    launch_reset(h->w.ctl, h->w.st, h->w.sec, h->plan.nnodes, Io{d, e, sigma, U, VT}, st);
+  };
+  if (h->opt.timing || !h->opt.use_graph || h->harvest) {
+    start_call();
+    return run_plan(h, st);
+  }
+  // replay the plan's captured sequence: it does not depend on the buffers,
+  // which the call's first launch hands over on the device, so only new sizes
+  // or options are captured (a capture is 100 to 200 launches and an
+  // instantiation; keyed on the buffers it was paid by every call that brought
+  // new ones: 130 us at n = 100, 0.5 ms at n = 16384)
+  if (!h->gexec) {
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
-    drop_graph(h);
     if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
       return BDC_ERR_HIP;
     if (!h->side_stream && hipStreamCreateWithFlags(&h->side_stream, hipStreamNonBlocking) != hipSuccess)
@@ -573,7 +571,7 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
     if (!h->ev_fork && hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
     if (!h->ev_join && hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
     if (hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return BDC_ERR_HIP;
-    const int rc = run_plan(h, d, e, sigma, U, VT, h->cap_stream, h->tune.streams == 2 ? h->side_stream : nullptr);
+    const int rc = run_plan(h, h->cap_stream, h->tune.streams == 2 ? h->side_stream : nullptr);
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(h->cap_stream, &g);
     if (rc != BDC_OK || ec != hipSuccess || !g) {
@@ -586,8 +584,8 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
       h->gexec = nullptr;
       return BDC_ERR_HIP;
     }
-    for (int i = 0; i < 5; ++i) h->gkey[i] = key[i];
   }
+  start_call();
   if (hipGraphLaunch(h->gexec, st) != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
   h->have_call = true;

@@ -44,8 +44,6 @@ Work make_work(Tmp& t, int64_t n) {
   const size_t N1 = (size_t)n, N2 = (size_t)(n * n);
   w.Uw = t.alloc<double>(N2);
   w.Vw = t.alloc<double>(N2);
-  w.GU = t.alloc<double>(N2);
-  w.GV = t.alloc<double>(N2);
   w.UM = t.alloc<double>(N2);
   w.VM = t.alloc<double>(N2);
   w.sig = t.alloc<double>(N1);
@@ -129,12 +127,10 @@ int bdc_step_leaf(bdc_handle_t h, int m, int s, const double* d, const double* e
   Work w = make_work(t, ld);
   LeafDesc* ld_dev = t.alloc<LeafDesc>(1);
   if (!t.ok) return BDC_ERR_NOMEM;
-  w.d = d;
-  w.e = e;
   w.max_leaf_sweeps = mls;
   LeafDesc L{0, 0, ld, 0, m, s};
   if (hipMemcpy(ld_dev, &L, sizeof(L), hipMemcpyHostToDevice) != hipSuccess) return BDC_ERR_HIP;
-  launch_reset(w.ctl, w.st, w.sec, 1, st);
+  launch_reset(w.ctl, w.st, w.sec, 1, Io{d, e, nullptr, nullptr, nullptr}, st);
   launch_leaf(ld_dev, 1, m, w, st);
   if (hipMemcpy2DAsync(W, sizeof(double) * m, w.Uw, sizeof(double) * ld, sizeof(double) * m, m,
                        hipMemcpyDeviceToDevice, st) != hipSuccess)
@@ -175,8 +171,6 @@ int bdc_step_deflate(bdc_handle_t h, int m, int s, const double* sig, const doub
   double* ee = t.alloc<double>(ld);
   NodeDesc* nd_dev = t.alloc<NodeDesc>(1);
   if (!t.ok) return BDC_ERR_NOMEM;
-  w.d = dd;
-  w.e = ee;
   // the two rows of the children's right bases the merge reads
   if (hipMemcpy2D(w.Vw + (k - 1), sizeof(double) * ld, qrow1, sizeof(double), sizeof(double), k,
                   hipMemcpyDeviceToDevice) != hipSuccess)
@@ -200,7 +194,7 @@ int bdc_step_deflate(bdc_handle_t h, int m, int s, const double* sig, const doub
       hipMemcpy(ee, eh.data(), sizeof(double) * ld, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(nd_dev, &nd, sizeof(nd), hipMemcpyHostToDevice) != hipSuccess)
     return BDC_ERR_HIP;
-  launch_reset(w.ctl, w.st, w.sec, 1, st);
+  launch_reset(w.ctl, w.st, w.sec, 1, Io{dd, ee, nullptr, nullptr, nullptr}, st);
   launch_prep(nd_dev, 1, m, w, st);
   int rc = finish(st);
   if (rc != BDC_OK) return rc;
@@ -260,7 +254,7 @@ int bdc_step_secular_start(bdc_handle_t h, int N, const double* d, const double*
       hipMemcpy(w.st, &ns, sizeof(ns), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(nd_dev, &nd, sizeof(nd), hipMemcpyHostToDevice) != hipSuccess)
     return BDC_ERR_HIP;
-  launch_reset(w.ctl, w.st, w.sec, 1, st);
+  launch_reset(w.ctl, w.st, w.sec, 1, Io{}, st);
   launch_secular(nd_dev, 1, N, w, st);
   return finish(st);
 }

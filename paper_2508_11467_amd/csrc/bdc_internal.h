@@ -88,11 +88,23 @@ struct SecCount {
   unsigned long long capped;
 };
 
-// Per-call device counters (rare events only; the statistics are per node
-// and per leaf).
+// The caller's buffers of one call.  Kernels read them from device memory,
+// where the call's first launch puts them, so that one captured launch
+// sequence serves every call of its sizes whatever buffers it is given.
+struct Io {
+  const double* d;  // inputs, packed per problem at vec_off
+  const double* e;
+  double* sigma;
+  double* U;   // (until the final pass) the gathered kept columns of U
+  double* VT;  // and of V
+};
+
+// Per-call device state: the buffers, and counters (rare events only; the
+// statistics are per node and per leaf).
 struct Ctl {
   int32_t nonfinite;
   int32_t leaf_capped;
+  Io io;
 };
 
 // Split-precision update products: bfloat16 slice planes per side (0 U,
@@ -135,14 +147,10 @@ struct CrtWork {
   int L;                           // moduli
 };
 
-// Device pointers of one call (passed to every kernel by value).
+// Device pointers of the workspace (passed to every kernel by value).
 struct Work {
-  const double* d;  // inputs, packed per problem at vec_off
-  const double* e;
   double* Uw;  // working vectors, packed per problem at mat_off
   double* Vw;
-  double* GU;  // gathered kept columns (caller's U buffer)
-  double* GV;  // (caller's VT buffer)
   double* UM;
   double* VM;
   // per node-position arrays (packed at vec_off)
@@ -221,7 +229,8 @@ struct Tuning {
 size_t work_layout(Work* w, char* base, int64_t tn, int64_t tn2, int nnodes);
 
 // ---- launchers (defined next to their kernels) ----
-void launch_reset(Ctl* ctl, NodeState* st, SecCount* sec, int nnodes, hipStream_t st_);
+// counters to zero, io to the device: before anything else of a call
+void launch_reset(Ctl* ctl, NodeState* st, SecCount* sec, int nnodes, const Io& io, hipStream_t st_);
 // leaves of at most max_m rows
 void launch_leaf(const LeafDesc* leaves, int nleaves, int max_m, const Work& w, hipStream_t st);
 void launch_prep(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
@@ -236,11 +245,11 @@ void launch_update(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, 
 // Final pass: work items of U (groups of final_u_cols columns) and of V^T
 // (bands x groups of column tiles, as above), numbered per problem from
 // uitem_off / vitem_off, with item -> problem tables uprob / vprob.
-void launch_final_single(int64_t n, const Work& w, double* sigma, double* U, double* VT, hipStream_t st);
+void launch_final_single(int64_t n, const Work& w, hipStream_t st);
 void launch_final(const int64_t* prob_n, const int64_t* prob_vec, const int64_t* prob_mat,
                   const int64_t* uitem_off, const int64_t* vitem_off, const int32_t* uprob,
                   const int32_t* vprob, int64_t total_uitems, int64_t total_vitems, const Work& w,
-                  double* sigma, double* U, double* VT, hipStream_t st);
+                  hipStream_t st);
 // device and iteration options of a handle (BDC_OK or BDC_ERR_INVALID_HANDLE)
 int handle_info(bdc_handle_t h, int* device, int* max_secular_iters, int* max_leaf_sweeps);
 // the handle's secular small-problem threshold (launch tuning)

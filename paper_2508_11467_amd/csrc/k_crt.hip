@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) void k_crt_lvl_amax(const NodeDesc* __restrict
   const int row = rb * 256 + threadIdx.x, k0 = kc * 256;
   if (row >= h.rows || k0 >= h.K) return;
   const int64_t ld = nd.ld;
-  const double* G = (h.isV ? w.GV : w.GU) + nd.mat_off + (nd.r0 + h.rowoff + row) + (int64_t)(nd.r0 + h.kb) * ld;
+  const double* G = (h.isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off + (nd.r0 + h.rowoff + row) + (int64_t)(nd.r0 + h.kb) * ld;
   double mx = 0.0;
   const int ke = min(h.K, k0 + 256);
   for (int k = k0; k < ke; ++k) mx = fmax(mx, fabs(G[(int64_t)k * ld]));
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) void k_crt_lvl_splita(const NodeDesc* __restri
   const int prow = nd.r0 + h.rowoff + r;
   const int E = row_exp(w.crt.amax[h.isV][prow], beta);
   if (k0 == 0) w.crt.Ea[h.isV][prow] = E;
-  const double* G = (h.isV ? w.GV : w.GU) + nd.mat_off + (nd.r0 + h.rowoff) + (int64_t)(nd.r0 + h.kb) * ld;
+  const double* G = (h.isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off + (nd.r0 + h.rowoff) + (int64_t)(nd.r0 + h.kb) * ld;
   split16<L>(G, 1, ld, h.rows, h.K, r, k0, E, w.crt.A[h.isV] + (int64_t)prow * w.crt.P, w.crt.planeA);
 }
 

@@ -61,8 +61,8 @@ __device__ inline MergeHead merge_head(const NodeDesc& nd, const Work& w) {
   const double* V = w.Vw + nd.mat_off;
   // the middle row of the split: alpha in the left child's last column,
   // beta in the right child's first column
-  const double alpha = w.d[pv + r0 + k - 1];
-  const double beta = w.e[pv + r0 + k - 1];
+  const double alpha = w.ctl->io.d[pv + r0 + k - 1];
+  const double beta = w.ctl->io.e[pv + r0 + k - 1];
   double vmax = fmax(fmax(fabs(alpha), fabs(beta)), fmax(w.sig[vo + k - 2], w.sig[vo + m - 1]));
   MergeHead h;
   h.p = 1.0;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void k_zsort(const NodeDesc* __restrict__ node
   if ((int)blockIdx.y * kBlock >= m) return;
   const MergeHead h = merge_head(nd, w);
   if (blockIdx.y == 0 && threadIdx.x == 0 &&
-      !(fabs(w.d[pv + r0 + k - 1]) <= DBL_MAX && fabs(w.e[pv + r0 + k - 1]) <= DBL_MAX))
+      !(fabs(w.ctl->io.d[pv + r0 + k - 1]) <= DBL_MAX && fabs(w.ctl->io.e[pv + r0 + k - 1]) <= DBL_MAX))
     atomicOr(&w.ctl->nonfinite, 1);
   const double* sig = w.sig + vo;
   double lmax = 0.0;
@@ -262,7 +262,7 @@ __device__ double zsort_node(const NodeDesc& nd, const Work& w, const MergeHead&
   const int64_t ld = nd.ld, pv = nd.vec_off, vo = nd.vec_off + nd.r0;
   const double* V = w.Vw + nd.mat_off;
   const int t = threadIdx.x;
-  if (t == 0 && !(fabs(w.d[pv + r0 + k - 1]) <= DBL_MAX && fabs(w.e[pv + r0 + k - 1]) <= DBL_MAX))
+  if (t == 0 && !(fabs(w.ctl->io.d[pv + r0 + k - 1]) <= DBL_MAX && fabs(w.ctl->io.e[pv + r0 + k - 1]) <= DBL_MAX))
     atomicOr(&w.ctl->nonfinite, 1);
   const double* sig = w.sig + vo;
   int pc[Q];

@@ -195,8 +195,8 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
 
   // load and scale by a power of two
   double dv = 0.0, ev = 0.0;
-  if (lane < m) dv = w.d[pv + r0 + lane];
-  if (lane < m - 1 + s) ev = w.e[pv + r0 + lane];
+  if (lane < m) dv = w.ctl->io.d[pv + r0 + lane];
+  if (lane < m - 1 + s) ev = w.ctl->io.e[pv + r0 + lane];
   // every entry of d and e belongs to exactly one leaf or one merge's middle
   // row, so leaves and merges between them check all of the input
   const bool bad = __any(!(fabs(dv) <= 1.79769313486231570e308) || !(fabs(ev) <= 1.79769313486231570e308));
@@ -405,10 +405,11 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
   if (lane == 0) w.leaf_fl[blockIdx.x] = 6ull * (nrot_w * (unsigned long long)m + nrot_q * (unsigned long long)ms);
 }
 
-__global__ __launch_bounds__(256) void k_reset(Ctl* ctl, NodeState* st, SecCount* sec, int nnodes) {
+__global__ __launch_bounds__(256) void k_reset(Ctl* ctl, NodeState* st, SecCount* sec, int nnodes, Io io) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->nonfinite = 0;
     ctl->leaf_capped = 0;
+    ctl->io = io;
   }
   for (int i = blockIdx.x * 256 + threadIdx.x; i < nnodes; i += gridDim.x * 256) {
     st[i].zmax_bits = 0ull;
@@ -420,11 +421,11 @@ __global__ __launch_bounds__(256) void k_reset(Ctl* ctl, NodeState* st, SecCount
 
 }  // namespace
 
-void launch_reset(Ctl* ctl, NodeState* nst, SecCount* sec, int nnodes, hipStream_t st) {
+void launch_reset(Ctl* ctl, NodeState* nst, SecCount* sec, int nnodes, const Io& io, hipStream_t st) {
   int blocks = (nnodes + 255) / 256;
   if (blocks < 1) blocks = 1;
   if (blocks > 64) blocks = 64;
-  hipLaunchKernelGGL(k_reset, dim3(blocks), dim3(256), 0, st, ctl, nst, sec, nnodes);
+  hipLaunchKernelGGL(k_reset, dim3(blocks), dim3(256), 0, st, ctl, nst, sec, nnodes, io);
 }
 
 void launch_leaf(const LeafDesc* leaves, int nleaves, int max_m, const Work& w, hipStream_t st) {

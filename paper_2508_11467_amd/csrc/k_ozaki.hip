@@ -266,7 +266,7 @@ __global__ __launch_bounds__(64) void k_oz_rows(const NodeDesc* __restrict__ nod
   const int row = blockIdx.y * 64 + threadIdx.x;
   if (row >= h.rows) return;
   const int64_t ld = nd.ld;
-  const double* G = (h.isV ? w.GV : w.GU) + nd.mat_off;
+  const double* G = (h.isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off;
   const double* src = G + (nd.r0 + h.rowoff + row) + (int64_t)(nd.r0 + h.kb) * ld;
   const int side = h.isV;
   const int64_t prow = nd.r0 + h.rowoff + row;

@@ -96,8 +96,8 @@ __global__ __launch_bounds__(256) void k_gather(const NodeDesc* __restrict__ nod
   const int64_t ld = nd.ld, pv = nd.vec_off, vo = nd.vec_off + nd.r0;
   const double* U = w.Uw + nd.mat_off;
   const double* V = w.Vw + nd.mat_off;
-  double* GU = w.GU + nd.mat_off;
-  double* GV = w.GV + nd.mat_off;
+  double* GU = w.ctl->io.U + nd.mat_off;
+  double* GV = w.ctl->io.VT + nd.mat_off;
   const int64_t total = (int64_t)N * R;
   const int64_t units = (total + kGatherSlab - 1) / kGatherSlab;
   const double inv_r = 1.0 / (double)R;
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256, update_waves_per_eu(TM)) void k_update(const N
   const int ke = bottom ? N : n1 + 1 + n2;
   const int K = ke - kb;
   const int rowoff = bottom ? k : 0;
-  const double* G = (isV ? w.GV : w.GU) + nd.mat_off;
+  const double* G = (isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off;
   const double* Mv = (isV ? w.VM : w.UM) + nd.mat_off;
   const double* A = G + (r0 + rowoff) + (int64_t)(r0 + kb) * ld;
   const double* B = Mv + (r0 + kb) + (int64_t)r0 * ld;
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256, 2) void k_update2(const NodeDesc* __restrict__
   const int ke = bottom ? N : n1 + 1 + n2;
   const int K = ke - kb;
   const int rowoff = bottom ? k : 0;
-  const double* G = (isV ? w.GV : w.GU) + nd.mat_off;
+  const double* G = (isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off;
   const double* Mv = (isV ? w.VM : w.UM) + nd.mat_off;
   const double* A = G + (r0 + rowoff) + (int64_t)(r0 + kb) * ld;
   const double* B = Mv + (r0 + kb) + (int64_t)r0 * ld;
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256) void k_update_wave(const NodeDesc* __restrict_
     const int ke = bottom ? N : n1 + 1 + n2;
     const int K = ke - kb;
     const int rowoff = bottom ? k : 0;
-    const double* G = (isV ? w.GV : w.GU) + nd.mat_off;
+    const double* G = (isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off;
     const double* Mv = (isV ? w.VM : w.UM) + nd.mat_off;
     const double* __restrict__ A = G + (r0 + rowoff) + (int64_t)(r0 + kb) * ld;
     const double* __restrict__ Bm = Mv + (r0 + kb) + (int64_t)r0 * ld;
@@ -602,7 +602,7 @@ __global__ __launch_bounds__(256, update_waves_per_eu(TM)) void k_update_flat(co
     const int ke = bottom ? N : n1 + 1 + n2;
     const int rowoff = bottom ? nd.k : 0;
     const int64_t ld = nd.ld, vo = nd.vec_off + nd.r0;
-    const double* G = (isV ? w.GV : w.GU) + nd.mat_off;
+    const double* G = (isV ? w.ctl->io.VT : w.ctl->io.U) + nd.mat_off;
     const double* Mv = (isV ? w.VM : w.UM) + nd.mat_off;
     const double* A = G + (nd.r0 + rowoff) + (int64_t)(nd.r0 + kb) * ld;
     const double* B = Mv + (nd.r0 + kb) + (int64_t)nd.r0 * ld;
@@ -650,8 +650,9 @@ __global__ __launch_bounds__(256) void k_final_u(const int64_t* __restrict__ pn,
                                                  const int64_t* __restrict__ pvec,
                                                  const int64_t* __restrict__ pmat,
                                                  const int64_t* __restrict__ uitem_off,
-                                                 const int32_t* __restrict__ uprob, Work w, double* sigma,
-                                                 double* U) {
+                                                 const int32_t* __restrict__ uprob, Work w) {
+  double* const sigma = w.ctl->io.sigma;
+  double* const U = w.ctl->io.U;
   __shared__ int64_t s_pc[64];
   __shared__ int s_ul[64], s_uh[64];
   const int64_t item = blockIdx.x;
@@ -747,7 +748,8 @@ __global__ __launch_bounds__(256) void k_final_vt(const int64_t* __restrict__ pn
                                                   const int64_t* __restrict__ pvec,
                                                   const int64_t* __restrict__ pmat,
                                                   const int64_t* __restrict__ vitem_off,
-                                                  const int32_t* __restrict__ vprob, Work w, double* VT) {
+                                                  const int32_t* __restrict__ vprob, Work w) {
+  double* const VT = w.ctl->io.VT;
   static_assert(kVtBand == kBlock && kVtTile == 16, "one vector per thread, eight threads per run");
   constexpr int kPass = kVtBand / (kBlock / 8);  // vectors per thread in the reads
   __shared__ double tileS[kVtTile][kVtBand + 1];
@@ -824,7 +826,8 @@ __global__ __launch_bounds__(256) void k_final_vt(const int64_t* __restrict__ pn
 // ---- single problem: 4 KB chunks, XCD-aligned
 // Per output index tv (descending values): the source column of the tv-th
 // largest value with its row supports in U and in V; sigma written here.
-__global__ __launch_bounds__(256) void k_final_meta(int64_t n, Work w, double* sigma) {
+__global__ __launch_bounds__(256) void k_final_meta(int64_t n, Work w) {
+  double* const sigma = w.ctl->io.sigma;
   const int64_t tv = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (tv >= n) return;
   const int64_t src = n - 1 - tv;
@@ -860,7 +863,8 @@ __device__ inline int64_t div_n(int64_t e, int64_t n, double inv_n) {
 }
 
 // U: chunks c0 + 8q, c0 = (b / 8) 8 kFinalR + b mod 8
-__global__ __launch_bounds__(256) void k_final_u_chunks(int64_t n, Work w, double* U) {
+__global__ __launch_bounds__(256) void k_final_u_chunks(int64_t n, Work w) {
+  double* const U = w.ctl->io.U;
   const int64_t total = n * n;
   const double inv_n = 1.0 / (double)n;
   const int64_t c0 = (int64_t)(blockIdx.x >> 3) * (8 * kFinalR) + (blockIdx.x & 7);
@@ -912,7 +916,8 @@ __global__ __launch_bounds__(256) void k_final_u_chunks(int64_t n, Work w, doubl
 // before the current group's stores.
 constexpr int kVtJ = 8;
 
-__global__ __launch_bounds__(256) void k_final_vt_chunks(int64_t n, Work w, double* VT) {
+__global__ __launch_bounds__(256) void k_final_vt_chunks(int64_t n, Work w) {
+  double* const VT = w.ctl->io.VT;
   const double* Vw = w.Vw;
   const int4* fv = w.fin + n;
   const int64_t cpc = n / kFinalChunk;  // chunks per output column
@@ -1050,20 +1055,20 @@ void launch_gemm_plain(int M, int N, int K, const double* A, int lda, const doub
 void launch_final(const int64_t* prob_n, const int64_t* prob_vec, const int64_t* prob_mat,
                   const int64_t* uitem_off, const int64_t* vitem_off, const int32_t* uprob,
                   const int32_t* vprob, int64_t total_uitems, int64_t total_vitems, const Work& w,
-                  double* sigma, double* U, double* VT, hipStream_t st) {
+                  hipStream_t st) {
   if (total_uitems <= 0) return;
   hipLaunchKernelGGL(k_final_u, dim3((unsigned)total_uitems), dim3(kBlock), 0, st, prob_n, prob_vec, prob_mat,
-                     uitem_off, uprob, w, sigma, U);
+                     uitem_off, uprob, w);
   hipLaunchKernelGGL(k_final_vt, dim3((unsigned)total_vitems), dim3(kBlock), 0, st, prob_n, prob_vec, prob_mat,
-                     vitem_off, vprob, w, VT);
+                     vitem_off, vprob, w);
 }
 
-void launch_final_single(int64_t n, const Work& w, double* sigma, double* U, double* VT, hipStream_t st) {
+void launch_final_single(int64_t n, const Work& w, hipStream_t st) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_final_meta, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, n, w, sigma);
+  hipLaunchKernelGGL(k_final_meta, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, n, w);
   const int64_t chunks = (n * n + kFinalChunk - 1) / kFinalChunk;
   const int64_t groups = (chunks + 8 * kFinalR - 1) / (8 * kFinalR);
-  hipLaunchKernelGGL(k_final_u_chunks, dim3((unsigned)(groups * 8)), dim3(kBlock), 0, st, n, w, U);
+  hipLaunchKernelGGL(k_final_u_chunks, dim3((unsigned)(groups * 8)), dim3(kBlock), 0, st, n, w);
   // V^T: one workgroup per (chunk row, group of kVtJ columns), a multiple of
   // the chunks per output column and so of 8.  With non-temporal stores,
   // short-lived workgroups stream best: 0.677 ms for the two passes of n =
@@ -1071,7 +1076,7 @@ void launch_final_single(int64_t n, const Work& w, double* sigma, double* U, dou
   // walking column ranges (with plain stores three workgroups per CU were).
   const int64_t cpc = n / kFinalChunk;
   const int64_t gv = cpc * (n / kVtJ);
-  hipLaunchKernelGGL(k_final_vt_chunks, dim3((unsigned)gv), dim3(kBlock), 0, st, n, w, VT);
+  hipLaunchKernelGGL(k_final_vt_chunks, dim3((unsigned)gv), dim3(kBlock), 0, st, n, w);
 }
 
 }  // namespace bdc

@@ -288,3 +288,39 @@ def test_full_size_n32768_normal(gpu, start):
         assert st["levels"] == 10
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("streams", [1, 2])
+@pytest.mark.parametrize("n", [100, 777, 4096])
+def test_new_buffers_between_calls(gpu, n, streams):
+    """One handle, calls with other inputs and outputs right after each other
+    (nothing waits in between), on one stream and on two that wait for each
+    other: every call's results are those of a handle of its own."""
+    import torch
+
+    from paper_2508_11467_amd import inputs
+    from paper_2508_11467_amd.api import Solver
+    data = [[torch.from_numpy(x).cuda() for x in inputs.uniform(n, 40 + i)] for i in range(3)]
+    want = []
+    for d, e in data:
+        s = Solver(0)
+        want.append([x.clone() for x in s.svd(d, e)])
+        s.close()
+    s = Solver(0)
+    s.set_tuning(**{**s.tuning(), "streams": streams})
+    other = torch.cuda.Stream()
+    got = []
+    for rep in range(2):
+        for i, (d, e) in enumerate(data):
+            if rep == 1 and i == 1:
+                other.wait_stream(torch.cuda.current_stream())
+                with torch.cuda.stream(other):
+                    got.append((i, s.svd(d, e)))
+                torch.cuda.current_stream().wait_stream(other)
+            else:
+                got.append((i, s.svd(d, e)))
+    torch.cuda.synchronize()
+    for i, out in got:
+        for x, y in zip(out, want[i]):
+            assert torch.equal(x, y)
+    s.close()
