@@ -304,8 +304,8 @@ int bdc_apply_reflectors_noalloc(bdc_handle_t handle, int trans, int m, int p, i
  * pivot at column i + 1); d (n), e (n - 1), tauq (n), taup (n, taup[n-1] =
  * 0) are device outputs.  Panels of `block` columns and rows (1..32; 0 = 32)
  * are reduced by one cooperative grid each (eq. bidiag-y-k3, bidiag-x-k3:
- * two passes over the panel-start trailing matrix per column, five grid
- * barriers per column), then the trailing matrix is updated by the one
+ * two passes over the panel-start trailing matrix and two sums over the grid
+ * per column), then the trailing matrix is updated by the one
  * product A - P Q^T (eq. bidiag-A-trail3) on the FP64 matrix cores.  With
  * bdc_svd(d, e) = U_2 Sigma V_2^T it gives the dense SVD: U = Q [U_2; 0] by
  * bdc_apply_reflectors on the column reflectors (y_rs = 1, y_cs = lda,
@@ -323,8 +323,8 @@ int bdc_gebrd(bdc_handle_t handle, int m, int n, double* A, int lda, double* d, 
  * overwritten with R on and above the diagonal and the Householder vectors
  * below it, tau (n, device) with their scalars -- LAPACK's geqrf storage,
  * H_i = I - tau_i y_i y_i^T with y_i = 1 at row i.  Blocked: panels of
- * `block` columns (1..64; 0 = 32) are factored on the GPU one column at a
- * time by a cooperative grid (one grid all-reduce per column), and the
+ * `block` columns (1..64; 0 = 32) are factored on the GPU by a
+ * cooperative grid (one sum over the grid per up to 8 columns), and the
  * trailing columns are updated by the panel's reflectors in the modified
  * compact WY form of eq. inv_t / larft_update (T^{-1} = Y^T Y, gemm, trsm,
  * gemm).  The rows below a panel's top block must fit the resident grid (at

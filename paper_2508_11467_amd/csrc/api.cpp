@@ -32,7 +32,7 @@ namespace {
 
 constexpr uint32_t kMagic = 0xBDC05EEDu;
 constexpr int kQrDefaultBlock = 32;  // panel width of bdc_geqrf when block = 0
-constexpr int kQrMaxGrid = 2048;     // workgroups of a QR panel, at most
+constexpr int kQrMaxGrid = 512;      // workgroups of a QR or reduction panel, at most
 
 enum Kind {
   kReset = 0, kLeaf, kPrep, kRotate, kGather, kStart, kSecular, kLowner, kVectors, kOrder, kUpdate, kUpdateOz,
@@ -106,9 +106,9 @@ struct bdc_handle_s {
   void* bt_arena = nullptr;   // back-transformation scratch (grown on demand)
   size_t bt_bytes = 0;
   void* bt_fixed = nullptr;   // this device's fixed scratch (allocation-free back-transformation)
-  void* qr_sync = nullptr;    // QR panel: grid-barrier state and partial sums
+  void* qr_sync = nullptr;    // QR panel: places of its sums over the grid
   size_t qr_sync_size = 0;
-  void* brd_work = nullptr;   // bidiagonal reduction: panel buffers, barrier state, partial sums
+  void* brd_work = nullptr;   // bidiagonal reduction: panel buffers, places of its sums over the grid
   size_t brd_bytes = 0;
   void* crt_arena = nullptr;  // int8 residue planes (single-problem solves)
   size_t crt_bytes = 0;

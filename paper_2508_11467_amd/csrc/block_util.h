@@ -12,6 +12,33 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// x plus lane-shifted x's by DPP (no LDS round trip): a shift or broadcast
+// `Ctrl` into the rows of 16 lanes that `Rows` names; lanes without a source
+// add zero.
+template <int Ctrl, int Rows>
+__device__ __forceinline__ double dpp_add(double x) {
+  return x + __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), Ctrl, Rows, 0xF, false),
+                              __builtin_amdgcn_update_dpp(0, __double2loint(x), Ctrl, Rows, 0xF, false));
+}
+
+// sum over each row of 16 lanes, in all of them
+__device__ __forceinline__ double row_sum(double x) {
+  x = dpp_add<0x128, 0xF>(x);  // row_ror:8
+  x = dpp_add<0x124, 0xF>(x);
+  x = dpp_add<0x122, 0xF>(x);
+  return dpp_add<0x121, 0xF>(x);
+}
+
+// sum over the wavefront, in lane 63
+__device__ __forceinline__ double wave_sum_last(double x) {
+  x = dpp_add<0x111, 0xF>(x);     // row_shr:1
+  x = dpp_add<0x112, 0xF>(x);
+  x = dpp_add<0x114, 0xF>(x);
+  x = dpp_add<0x118, 0xF>(x);     // lane 15 of a row: the row's sum
+  x = dpp_add<0x142, 0xA>(x);     // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+}
+
 __device__ inline double wave_maxd(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
   return v;

@@ -26,7 +26,7 @@
 //      the step's columns one reflector after the other, then the later
 //      columns together.
 // Panels of 32 columns of 20000 rows: 525 us with an all-reduce and three
-// passes over LDS per column, 135 us so (four all-reduces).
+// passes over LDS per column, 114 us so (four all-reduces).
 // Every wait of the all-reduce is bounded (a flag reports an expired wait and
 // the kernel ends), and the launch is cooperative, so all workgroups are
 // resident.
@@ -59,30 +59,17 @@ struct PanelLds {
   double W[kQrStep * kQrMaxB];       // W[i * 64 + k]: w of reflector i, column k of the panel
   double P[kQrMaxB];                 // the top block's part of M's row i
   double big[kQrStep];               // sum of the terms' sizes in M[i][i]
-  unsigned sh[3];
+  unsigned bad;                      // a wait of an all-reduce has expired
 };
 
-// sum over a wavefront, in lane 63 (row shifts, then the row totals)
-__device__ __forceinline__ double wave_sum_last(double x) {
-#define QR_DPP(ctrl, rows)                                                              \
-  x += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), ctrl, rows, 0xF, false), \
-                        __builtin_amdgcn_update_dpp(0, __double2loint(x), ctrl, rows, 0xF, false))
-  QR_DPP(0x111, 0xF);  // row_shr:1
-  QR_DPP(0x112, 0xF);  // row_shr:2
-  QR_DPP(0x114, 0xF);  // row_shr:4
-  QR_DPP(0x118, 0xF);  // row_shr:8
-  QR_DPP(0x142, 0xA);  // row_bcast:15 into rows 1 and 3
-  QR_DPP(0x143, 0xC);  // row_bcast:31 into rows 2 and 3
-#undef QR_DPP
-  return x;
-}
-
-// grid: G workgroups (cooperative), kQrBlock threads.  slots: 2 x G x kQrSums
-// doubles; gslots: 2 x grid_group_doubles(kQrSums).
+// grid: G workgroups (cooperative), kQrBlock threads.  slots: kGridSets x
+// kQrSums x G places; totals: two regions of kGridSets x kQrSums, this launch's
+// (`region`) all empty, the other, which the last launch used and did not
+// clear, emptied here for the next one.
 __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A, int64_t lda, int m, int j0, int b,
                                                      int rows_per_wg, double* __restrict__ tau,
-                                                     double* __restrict__ slots, double* __restrict__ gslots,
-                                                     GridSync* sync) {
+                                                     double* __restrict__ slots, double* __restrict__ totals,
+                                                     int region) {
   __shared__ PanelLds L;
   const int t = threadIdx.x, G = gridDim.x, g = blockIdx.x;
   const int ln = t & 63, wv = t >> 6;
@@ -101,8 +88,13 @@ __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A
     const int r = e % R, k = e / R;
     L.X[r * XS + k] = A[(r0 + r) + (int64_t)(j0 + k) * lda];
   }
+  if (g == 0)
+    for (int e = t; e < kGridSets * kQrSums; e += kQrBlock) grid_clear(totals + (region ^ 1) * kGridSets * kQrSums + e);
+  totals += region * kGridSets * kQrSums;
+  if (t == 0) L.bad = 0;
   __syncthreads();
-  int phase = 0;  // slot buffer of the next all-reduce
+  int set = 0, last = 0;    // the next all-reduce's set; sums of the last one
+  double* prev = nullptr;   // its totals
   for (int c = 0; c < b;) {
     if (c >= top) {  // no pivot row left: identities
       if (g == 0 && t < b - c) tau[j0 + c + t] = 0.0;
@@ -137,16 +129,19 @@ __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A
           if (i < s) part[i * nk] += acc[i];
     }
     __syncthreads();
-    double* sl = slots + (size_t)phase * G * kQrSums;
-    double* gsl = gslots + (size_t)phase * grid_group_doubles(kQrSums);
-    phase ^= 1;
     if (t < s * nk) {
       double v = 0.0;
 #pragma unroll
       for (int u = 0; u < kQrWaves; ++u) v += L.red[u * kQrSums + t];
-      sl[(size_t)g * kQrSums + t] = v;
+      L.M[t] = v;
     }
-    if (!grid_allreduce(sync, sl, gsl, kQrSums, s * nk, L.M, L.red, L.sh)) return;
+    grid_settle();
+    __syncthreads();
+    double* tot = totals + set * kQrSums;
+    if (!grid_sum<kQrBlock>(slots + (size_t)set * kQrSums * G, tot, prev, last, s * nk, L.M, &L.bad)) return;
+    prev = tot;
+    last = s * nk;
+    set = set == kGridSets - 1 ? 0 : set + 1;
     if (t < s) L.big[t] = L.M[t * nk + t];
     // the step's reflectors
     double sc[kQrStep];
@@ -258,7 +253,10 @@ __global__ __launch_bounds__(kQrBlock, 1) void k_qr_panel(double* __restrict__ A
     }
 }
 
-__global__ __launch_bounds__(256) void k_qr_sync_init(GridSync* s) { grid_sync_clear(s); }
+__global__ __launch_bounds__(256) void k_qr_clear(double* __restrict__ places, int64_t count) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256)
+    grid_clear(places + e);
+}
 
 // Q (m x ncols, ldq) = the identity's first ncols columns
 __global__ __launch_bounds__(256) void k_qr_eye(double* __restrict__ Q, int64_t ldq, int m, int ncols) {
@@ -271,8 +269,11 @@ __global__ __launch_bounds__(256) void k_qr_eye(double* __restrict__ Q, int64_t 
 
 }  // namespace
 
+// places: kGridSets sets of slots, then two regions of totals
+static size_t qr_places(int wgs) { return (size_t)kGridSets * kQrSums * (wgs + 2); }
+
 size_t qr_sync_bytes(int max_wg) {
-  return kGridSyncBytes + 2 * ((size_t)max_wg * kQrSums + grid_group_doubles(kQrSums)) * sizeof(double);
+  return qr_places(std::min(max_wg, kGridMaxWg)) * sizeof(double);
 }
 
 int qr_max_block() { return kQrMaxB; }
@@ -296,9 +297,15 @@ int qr_panel_grid(int device, int rows_below, int b, int* grid, int* rows_per_wg
 
 int launch_geqrf(int device, int m, int n, double* A, int lda, double* tau, int b, void* sync_buf, size_t sync_bytes,
                  const BtPlan& plan, void* bt_scratch, hipStream_t st) {
-  GridSync* sync = reinterpret_cast<GridSync*>(sync_buf);
-  double* slots = reinterpret_cast<double*>(reinterpret_cast<char*>(sync_buf) + kGridSyncBytes);
-  hipLaunchKernelGGL(k_qr_sync_init, dim3(1), dim3(256), 0, st, sync);
+  // totals first, then slots; every slot is empty again when a panel ends,
+  // whatever its grid
+  double* totals = reinterpret_cast<double*>(sync_buf);
+  double* slots = totals + 2 * kGridSets * kQrSums;
+  int G0 = 1, R0 = 0, region = 0;
+  if (qr_panel_grid(device, std::max(0, m - std::min(b, n)), std::min(b, n), &G0, &R0) != 0) return BDC_ERR_TOO_LARGE;
+  if (qr_sync_bytes(G0) > sync_bytes) return BDC_ERR_TOO_LARGE;
+  const int64_t places = (int64_t)qr_places(G0);
+  hipLaunchKernelGGL(k_qr_clear, dim3((unsigned)((places + 255) / 256)), dim3(256), 0, st, totals, places);
   for (int j0 = 0; j0 < n; j0 += b) {
     const int bw = std::min(b, n - j0);
     const int top = std::min(bw, m - j0);
@@ -307,11 +314,11 @@ int launch_geqrf(int device, int m, int n, double* A, int lda, double* tau, int 
     if (qr_panel_grid(device, rows_below, bw, &G, &R) != 0) return BDC_ERR_TOO_LARGE;
     if (qr_sync_bytes(G) > sync_bytes) return BDC_ERR_TOO_LARGE;
     int64_t lda64 = lda;
-    double* gslots = slots + 2 * (size_t)G * kQrSums;
-    void* args[] = {&A, &lda64, &m, &j0, const_cast<int*>(&bw), &R, &tau, &slots, &gslots, &sync};
+    void* args[] = {&A, &lda64, &m, &j0, const_cast<int*>(&bw), &R, &tau, &slots, &totals, &region};
     if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_qr_panel), dim3(G), dim3(kQrBlock), args, 0, st) !=
         hipSuccess)
       return BDC_ERR_HIP;
+    region ^= 1;
     // trailing columns: A_t <- H_{bw-1} ... H_0 A_t = Q_panel^T A_t
     const int nt = n - j0 - bw;
     if (nt > 0)

@@ -170,6 +170,25 @@ def test_gebrd_square_2048_spectrum(solver):
     assert err <= 1e-13 and res <= 1e-14 * np.sqrt(n)
 
 
+@pytest.mark.parametrize("m,n,block", [(8300, 40, 0), (8195, 33, 7), (515, 3, 2), (3, 2, 0), (17, 17, 32), (4099, 67, 32)])
+def test_gebrd_workgroup_shapes(solver, m, n, block):
+    """More and fewer than 16 rows or columns per workgroup, one workgroup,
+    odd row counts (the last row of a pass stands alone): the bidiagonal and
+    the reflectors reproduce A, and two runs agree bit for bit."""
+    g = np.random.default_rng(m + n)
+    A = g.standard_normal((m, n))
+    r1 = _gpu_gebrd(solver, A, block)
+    F, d, e, tq, tp = r1
+    Yq, Yp = _unpack(F, m, n)
+    B = np.zeros((m, n))
+    B[np.arange(n), np.arange(n)] = d
+    B[np.arange(n - 1), np.arange(1, n)] = e
+    QtAP = hh.apply_q(Yp, tp[:n - 1], hh.apply_q(Yq, tq, A, trans=True).T, trans=True).T
+    assert np.max(np.abs(QtAP - B)) <= 1e-13 * np.sqrt(m) * np.linalg.norm(A, 2)
+    for x, y in zip(r1, _gpu_gebrd(solver, A, block)):
+        assert np.array_equal(x, y)
+
+
 def test_gebrd_is_bitwise_reproducible(solver):
     """Partial sums cross workgroups through per-workgroup slots added in a
     fixed order, whichever workgroup arrives last: two runs on the same input
