@@ -483,16 +483,21 @@ int run_plan(bdc_handle_t h, hipStream_t st, hipStream_t side = nullptr) {
     // The rotations of the deflated pairs and the gather of the kept columns
     // (the U and V data) need only the deflation's lists; the secular solve,
     // the Löwner z and the vectors of M~ (the small matrices) need only the
-    // deflated values and z.  Neither chain reads what the other writes, so
-    // with a second stream they run side by side, joined before the update
+    // deflated values and z.  Neither chain reads what the other writes: the
+    // secular launch carries both, unless each stage is timed by itself; with
+    // a second stream the chains run side by side, joined before the update
     // products, which need both.
-    hipStream_t sr = side ? side : st;
-    if (side && (hipEventRecord(h->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, h->ev_fork, 0) != hipSuccess))
-      return BDC_ERR_HIP;
-    { Timer t(h, sr, kRotate); launch_rotate(L.dev, L.nnodes, L.max_m, w, sr); }
-    { Timer t(h, sr, kGather); launch_gather(L.dev, L.nnodes, L.max_m, w, sr); }
-    if (side && hipEventRecord(h->ev_join, side) != hipSuccess) return BDC_ERR_HIP;
-    { Timer t(h, st, kSecular); launch_secular(L.dev, L.nnodes, L.max_m, w, st); }
+    const bool apart = side || h->opt.timing;
+    if (apart) {
+      hipStream_t sr = side ? side : st;
+      if (side &&
+          (hipEventRecord(h->ev_fork, st) != hipSuccess || hipStreamWaitEvent(side, h->ev_fork, 0) != hipSuccess))
+        return BDC_ERR_HIP;
+      { Timer t(h, sr, kRotate); launch_rotate(L.dev, L.nnodes, L.max_m, w, sr); }
+      { Timer t(h, sr, kGather); launch_gather(L.dev, L.nnodes, L.max_m, w, sr); }
+      if (side && hipEventRecord(h->ev_join, side) != hipSuccess) return BDC_ERR_HIP;
+    }
+    { Timer t(h, st, kSecular); launch_secular(L.dev, L.nnodes, L.max_m, !apart, w, st); }
     if (h->harvest) launch_harvest(L.dev, L.nnodes, L.max_m, w, h->hv, st);
     { Timer t(h, st, kLowner); launch_lowner(L.dev, L.nnodes, L.max_m, w, st); }
     { Timer t(h, st, kVectors); launch_vectors(L.dev, L.nnodes, L.max_m, w, st); }
@@ -778,7 +783,9 @@ int bdc_get_info(bdc_handle_t h, int64_t* info, bdc_stats_t* stats) {
     double gb = 0.0;
     for (int i = 0; i < p.nnodes; ++i) {
       const NodeDesc& nd = p.host_nodes[i];
-      gb += 16.0 * sts[i].N * (2.0 * nd.m + nd.s);  // read + write, U and V columns
+      // read + write, U and V columns: the rows that the products read
+      const double top = nd.k, bottom = 2.0 * (nd.m - nd.k) + nd.s;
+      gb += 16.0 * ((sts[i].n1 + 1.0 + sts[i].n2) * 2.0 * top + (1.0 + sts[i].n2 + sts[i].n3) * bottom);
     }
     stats->gather_bytes = gb;
     // supports read by the final pass

@@ -255,7 +255,7 @@ int bdc_step_secular_start(bdc_handle_t h, int N, const double* d, const double*
       hipMemcpy(nd_dev, &nd, sizeof(nd), hipMemcpyHostToDevice) != hipSuccess)
     return BDC_ERR_HIP;
   launch_reset(w.ctl, w.st, w.sec, 1, Io{}, st);
-  launch_secular(nd_dev, 1, N, w, st);
+  launch_secular(nd_dev, 1, N, false, w, st);
   return finish(st);
 }
 

@@ -236,7 +236,8 @@ void launch_leaf(const LeafDesc* leaves, int nleaves, int max_m, const Work& w, 
 void launch_prep(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
 void launch_rotate(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
 void launch_gather(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
-void launch_secular(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
+// columns: the launch carries launch_rotate's and launch_gather's work as well
+void launch_secular(const NodeDesc* nodes, int nnodes, int max_m, bool columns, const Work& w, hipStream_t st);
 void launch_lowner(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
 void launch_vectors(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);
 void launch_order(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st);

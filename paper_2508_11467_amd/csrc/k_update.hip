@@ -24,6 +24,7 @@
 
 #include "bdc_internal.h"
 #include "block_util.h"
+#include "columns.h"
 #include "gemm128.h"
 
 namespace bdc {
@@ -42,105 +43,15 @@ inline int grid_y(int nnodes, int units, int cap_total) {
   return gy;
 }
 
-// ------------------------------------------------------------------ rotate
+// ------------------------------------------------------------------ rotate, gather
+// The stand-alone launches, for runs that time each stage or put the two on a
+// second stream; otherwise the secular launch carries both bodies.
 __global__ __launch_bounds__(256) void k_rotate(const NodeDesc* __restrict__ nodes, Work w) {
-  const NodeDesc nd = nodes[blockIdx.x];
-  const int nrot = w.st[nd.id].nrot;
-  if (nrot == 0) return;
-  const int m = nd.m, s = nd.s, r0 = nd.r0;
-  const int64_t ld = nd.ld, pv = nd.vec_off;
-  const int64_t rb = 2 * (nd.vec_off + nd.r0);
-  double* U = w.Uw + nd.mat_off;
-  double* V = w.Vw + nd.mat_off;
-  for (int row = blockIdx.y * kBlock + threadIdx.x; row < m + s; row += gridDim.y * kBlock) {
-    const int gr = r0 + row;
-    const bool inU = row < m;
-    // zero-fill the touched columns outside their current support
-    for (int q = 0; q < nrot; ++q) {
-      const bool both = w.rot_pos[rb + 2 * q] != 0;
-      for (int h = 0; h < 2; ++h) {
-        const int pc = w.rot_col[rb + 2 * q + h];
-        if (both && inU && (gr < w.ulo[pv + pc] || gr >= w.uhi[pv + pc])) U[gr + pc * ld] = 0.0;
-        if (gr < w.vlo[pv + pc] || gr >= w.vhi[pv + pc]) V[gr + pc * ld] = 0.0;
-      }
-    }
-    for (int q = 0; q < nrot; ++q) {
-      const bool both = w.rot_pos[rb + 2 * q] != 0;
-      const int pp = w.rot_col[rb + 2 * q], pj = w.rot_col[rb + 2 * q + 1];
-      const double c = w.rot_cs[rb + 2 * q], sn = w.rot_cs[rb + 2 * q + 1];
-      if (both && inU) {
-        const double a = U[gr + pp * ld], b = U[gr + pj * ld];
-        U[gr + pp * ld] = c * a + sn * b;
-        U[gr + pj * ld] = -sn * a + c * b;
-      }
-      const double a = V[gr + pp * ld], b = V[gr + pj * ld];
-      V[gr + pp * ld] = c * a + sn * b;
-      V[gr + pj * ld] = -sn * a + c * b;
-    }
-  }
+  rotate_node<false>(nodes[blockIdx.x], w, blockIdx.y, gridDim.y);
 }
 
-// ------------------------------------------------------------------ gather
-// The node's kept columns in update order, both sides, as one flattened
-// range of N (m + s) elements (column g, row r) -> g (m + s) + r; a workgroup
-// takes slabs of kGatherSlab consecutive elements (four per thread, loads
-// issued before the stores), so that few long columns and many short ones
-// alike fill the workgroups.  U rows run to m, V rows to m + s.
-constexpr int kGatherSlab = 4 * kBlock;
-
 __global__ __launch_bounds__(256) void k_gather(const NodeDesc* __restrict__ nodes, Work w) {
-  const NodeDesc nd = nodes[blockIdx.x];
-  const int N = w.st[nd.id].N;
-  const int m = nd.m, s = nd.s, r0 = nd.r0, k = nd.k;
-  const int R = m + s;
-  const int64_t ld = nd.ld, pv = nd.vec_off, vo = nd.vec_off + nd.r0;
-  const double* U = w.Uw + nd.mat_off;
-  const double* V = w.Vw + nd.mat_off;
-  double* GU = w.ctl->io.U + nd.mat_off;
-  double* GV = w.ctl->io.VT + nd.mat_off;
-  const int64_t total = (int64_t)N * R;
-  const int64_t units = (total + kGatherSlab - 1) / kGatherSlab;
-  const double inv_r = 1.0 / (double)R;
-  for (int64_t u = blockIdx.y; u < units; u += gridDim.y) {
-    double xu[4], xv[4];
-    int gq[4], rq[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t e = u * kGatherSlab + q * kBlock + threadIdx.x;
-      gq[q] = -1;
-      rq[q] = 0;
-      xu[q] = xv[q] = 0.0;
-      if (e >= total) continue;
-      int g = (int)((double)e * inv_r);
-      if ((int64_t)g * R > e) --g;
-      else if ((int64_t)(g + 1) * R <= e) ++g;
-      const int row = (int)(e - (int64_t)g * R);
-      gq[q] = g;
-      rq[q] = row;
-      const int i = w.gsurv[vo + g];
-      const int gr = r0 + row;
-      if (i == 0) {
-        // d = 0 position: left vector e_{k-1} (the middle row), right vector x1
-        xu[q] = (row == k - 1) ? 1.0 : 0.0;
-        xv[q] = V[gr + (int64_t)(r0 + k - 1) * ld];
-      } else {
-        const int64_t pc = w.scol[vo + i];
-        const int rf = w.srot[vo + i];
-        const bool fu = (rf & kRotU) != 0, fv = (rf & kRotV) != 0;
-        const int ul = fu ? r0 : w.ulo[pv + pc], uh = fu ? r0 + m : w.uhi[pv + pc];
-        const int vl = fv ? r0 : w.vlo[pv + pc], vh = fv ? r0 + m + s : w.vhi[pv + pc];
-        xu[q] = (row < m && gr >= ul && gr < uh) ? U[gr + pc * ld] : 0.0;
-        xv[q] = (gr >= vl && gr < vh) ? V[gr + pc * ld] : 0.0;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (gq[q] < 0) continue;
-      const int64_t off = r0 + rq[q] + (int64_t)(r0 + gq[q]) * ld;
-      if (rq[q] < m) GU[off] = xu[q];
-      GV[off] = xv[q];
-    }
-  }
+  gather_node<false>(nodes[blockIdx.x], w, blockIdx.y, gridDim.y);
 }
 
 // ------------------------------------------------------------------ order
@@ -973,15 +884,14 @@ __global__ __launch_bounds__(256) void k_final_vt_chunks(int64_t n, Work w) {
 
 void launch_rotate(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st) {
   if (nnodes <= 0) return;
-  const int gy = grid_y(nnodes, (max_m + 1 + kBlock - 1) / kBlock, 4096);
+  const int gy = grid_y(nnodes, rotate_units(max_m), 4096);
   hipLaunchKernelGGL(k_rotate, dim3(nnodes, gy), dim3(kBlock), 0, st, nodes, w);
 }
 
 void launch_gather(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, hipStream_t st) {
   if (nnodes <= 0) return;
-  // up to 65536 workgroups per level (a batch's top level of a few hundred
-  // 2048-value merges: 3.0 ms for its gathers against 3.1-3.4 with 8192)
-  const int gy = grid_y(nnodes, (int)std::min<int64_t>(65535, ((int64_t)max_m * (max_m + 1) + kGatherSlab - 1) / kGatherSlab), 65536);
+  // about 65536 workgroups per level
+  const int gy = grid_y(nnodes, (int)std::min<int64_t>(65535, gather_units(max_m)), 65536);
   hipLaunchKernelGGL(k_gather, dim3(nnodes, gy), dim3(kBlock), 0, st, nodes, w);
 }
 

@@ -195,6 +195,45 @@ def test_second_stream_gives_the_same_results(gpu, flat):
         two.close()
 
 
+@pytest.mark.parametrize("n", [33, 65, 130, 257, 520, 1025, 2100, 4096])
+@pytest.mark.parametrize("kind", ["equal_blocks", "zeros", "normal"])
+def test_columns_in_the_secular_launch(gpu, n, kind):
+    """The rotations and the gather as part of the secular launch give bitwise
+    what they give as launches of their own (a handle that times its stages),
+    on merges with close pairs (equal blocks) and values near zero, with NaN
+    left in the output buffers that the gathered columns pass through."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    d, e = inputs.normal(n, 60 + n)
+    if kind == "equal_blocks":
+        d, e = np.resize(d[:16], n), np.resize(e[:16], n - 1)
+    elif kind == "zeros":
+        d[::7] = 0.0
+    dt, et = torch.from_numpy(np.ascontiguousarray(d)).cuda(), torch.from_numpy(np.ascontiguousarray(e)).cuda()
+    res = []
+    for timing in (False, True):
+        s = Solver(0, leaf_size=16, timing=timing)
+        try:
+            out = [torch.full(sh, float("nan"), dtype=torch.float64, device="cuda") for sh in ((n,), (n, n), (n, n))]
+            r = s.svd(dt, et, out=out)
+            info, st = s.info()
+            assert info == 0
+            if kind != "normal" and n > 33:
+                assert st["rotations"] > 0
+            res.append([x.clone() for x in r])
+        finally:
+            s.close()
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
+    U, S, VT = res[0][1], res[0][0], res[0][2]
+    B = torch.diag(dt) + torch.diag(et, 1)
+    scale = float(S.max())
+    assert float((U * S @ VT - B).abs().max()) <= 1e-13 * scale * n ** 0.5
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    assert float((U.T @ U - eye).abs().max()) <= 1e-13 * n ** 0.5
+    assert float((VT @ VT.T - eye).abs().max()) <= 1e-13 * n ** 0.5
+
+
 def test_autotune_picks_a_valid_tuning(gpu):
     import torch
     from paper_2508_11467_amd.api import Solver
