@@ -76,6 +76,36 @@ def test_gemm_crt_integers_exact(solver):
         assert np.array_equal(C, ref), L
 
 
+@pytest.mark.parametrize("L", [13, 14, 15, 16])
+@pytest.mark.parametrize("M,N,K", [(255, 127, 63), (256, 128, 64), (257, 129, 65), (3, 255, 128), (259, 2, 192),
+                                   (513, 130, 256), (6, 6, 512)])
+def test_gemm_crt_largest_integers(solver, L, M, N, K):
+    """Integers of beta bits, the largest that the scaling leaves alone, of one
+    sign (the sums then come as near (prod m_l - 1)/2 as they can) and of both:
+    the exact sum rounded once, at the edges of the tiles, of the k stages and
+    of the words the residues are stored in."""
+    import torch
+    b = beta(L, K)
+    unit = 2 ** max(0, b - 53)
+    top = 2 ** min(b, 53) - 1
+    g = np.random.default_rng(M + N + K + L)
+    A = g.integers(top // 2 + 1, top, size=(M, K), endpoint=True).astype(object) * unit
+    B = g.integers(top // 2 + 1, top, size=(K, N), endpoint=True).astype(object) * unit
+    A[0, :] = top * unit
+    B[:, 0] = top * unit
+    A[1 % M :: 2] *= g.choice([-1, 1], size=A[1 % M :: 2].shape).astype(object)
+    B[:, 1 % N :: 3] *= g.choice([-1, 1], size=B[:, 1 % N :: 3].shape).astype(object)
+    if M > 2:
+        A[2, :] = -top * unit
+    C = solver.step_gemm_crt(torch.from_numpy(A.astype(np.float64)).cuda(), torch.from_numpy(B.astype(np.float64)).cuda(),
+                             L).cpu().numpy()
+    rows = sorted({0, 1 % M, 2 % M, 3 % M, min(M - 1, 31), min(M - 1, 128), max(0, M - 2), M - 1})
+    cols = sorted({0, 1 % N, 2 % N, 31 % N, 64 % N, max(0, N - 2), N - 1})
+    want = A[rows] @ B[:, cols]
+    ref = np.array([[float(int(x)) for x in r] for r in want])
+    np.testing.assert_array_equal(C[np.ix_(rows, cols)], ref)
+
+
 def test_gemm_crt_extreme_scales_and_zero_rows(solver):
     """Rows and columns spanning 10^-200 .. 10^200, an all-zero row and an
     all-zero column: the power-of-two scales keep each one's relative
