@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void k_crt_split(const double* __restrict__ X,
 // Two workgroups share a CU (72 KB of LDS, 184 registers a lane): one's first
 // copies, reductions and stores pass while the other multiplies.  n = 6000 with
 // nothing deflated (16 moduli): the products of all levels 6.5 -> 3.6 ms, of the
-// last one 3.3 -> 2.2 (3.1 POP/s).  256 x 256 tiles, which fill a CU alone:
+// last one 3.3 -> 2.2 (1.8 POP/s).  256 x 256 tiles, which fill a CU alone:
 // 4.3 and 2.5; the stores straight from the accumulators, 32 columns an
 // instruction: 6.5 and 2.8.
 constexpr int kTile = 256, kTileN = 128, kKs = 64, kRing = 3;

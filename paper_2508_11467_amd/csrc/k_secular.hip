@@ -1,7 +1,7 @@
 // Merge stage after deflation (Algorithm 4, the GPU-based lasd3), entirely
 // on the GPU:
-//   k_secular  roots of the secular equation (eq. M-svd-val), one lane per
-//              root.  The paper solves them on CPU threads with LAPACK's
+//   k_secular  roots of the secular equation (eq. M-svd-val), one or several
+//              lanes per root.  The paper solves them on CPU threads with LAPACK's
 //              lasd4; here each root is bracketed, its origin pole chosen by
 //              the sign of f at the interval midpoint (in omega^2) -- or,
 //              with the learned start, by the half of the interval holding
@@ -36,6 +36,7 @@ namespace {
 constexpr double kEps = 0x1p-52;
 
 constexpr int kSecRoots = 64;    // roots per workgroup (one per lane)
+constexpr int kSecFew = 16;      // rounds with at most this many roots share the terms
 constexpr int kSecWaves = 4;     // wavefronts splitting the pole sums
 constexpr int kSecChunk = 512;   // poles staged in LDS per wavefront
 
@@ -59,18 +60,19 @@ __device__ inline void sum_terms(const double* __restrict__ dj, const double* __
                                  int count, double ov, double tau, Part& P) {
   int q = 0;
   for (; q + 4 <= count; q += 4) {
-    double t[4], r[4];
+    double z4[4], t[4], r[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = j0 + (q + u) * step;
       const double dd = dj[j];
       const double del = ((dd - ov) - tau) * ((dd + ov) + tau);  // d_j^2 - omega^2
       r[u] = recip(del);
-      t[u] = zz[j] * r[u];
+      z4[u] = zz[j];
+      t[u] = z4[u] * r[u];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      P.s += t[u];
+      P.s = fma(z4[u], r[u], P.s);
       P.ds = fma(t[u], r[u], P.ds);
       P.E += fabs(t[u]);
     }
@@ -81,10 +83,82 @@ __device__ inline void sum_terms(const double* __restrict__ dj, const double* __
     const double del = ((dd - ov) - tau) * ((dd + ov) + tau);
     const double r = recip(del);
     const double t = zz[j] * r;
-    P.s += t;
+    P.s = fma(zz[j], r, P.s);
     P.ds = fma(t, r, P.ds);
     P.E += fabs(t);
   }
+}
+
+// The same sums of up to RP roots (a power of two) by one wavefront, for the
+// rounds in which few roots are left: lane / P is a lane's root slot (P = 64 /
+// RP), its lanes take P consecutive terms of the root's sequence -- the left
+// poles upwards, then the right ones downwards -- and hand (z_j^2, the
+// reciprocal) on in LDS, where every lane of the slot adds them up one by one
+// in that order.  So a sum is the same whichever way a round is done; the 70
+// cycles of a term's reciprocal are shared by P lanes, and what is left per term
+// is the additions (about 50 cycles with RP = 16 and 30 with 4, against 85).
+// pole(j, d, zz) fetches pole j in [q0, q1); buf holds RP (2 P + 1) pairs.
+template <int RP, class Fetch>
+__device__ inline void sum_shared(double2* buf, int q0, int q1, int lp, double ov, double tau, Fetch pole, Part& PL,
+                                  Part& PR) {
+  constexpr int P = 64 / RP, C = 2 * P;  // terms per step
+  const int lane = threadIdx.x & 63, sub = lane % P;
+  double2* mine = buf + lane / P * (C + 1);
+  const int Q = q1 - q0;
+  if (Q <= 0) return;
+  const int nl = min(max(lp + 1 - q0, 0), Q);
+  double zz[2], r[2], dn[2], zn[2];
+  auto fetch = [&](int p0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int p = min(p0 + u * P + sub, Q - 1);
+      pole(p < nl ? q0 + p : q1 - 1 - (p - nl), dn[u], zn[u]);
+    }
+  };
+  auto terms = [&] {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      zz[u] = zn[u];
+      r[u] = recip(((dn[u] - ov) - tau) * ((dn[u] + ov) + tau));
+    }
+  };
+  Part A{0.0, 0.0, 0.0};
+  auto add = [&](const double2 v) {
+    const double t = v.x * v.y;
+    A.s = fma(v.x, v.y, A.s);
+    A.ds = fma(t, v.y, A.ds);
+    A.E += fabs(t);
+  };
+  fetch(0);
+  terms();
+  fetch(C);
+  for (int p0 = 0; p0 < Q; p0 += C) {
+    __builtin_amdgcn_wave_barrier();
+    mine[sub] = make_double2(zz[0], r[0]);
+    mine[P + sub] = make_double2(zz[1], r[1]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    terms();
+    fetch(p0 + 2 * C);
+    if (p0 + C <= Q && !__any(nl > p0 && nl < p0 + C && nl < Q)) {
+      if (nl == p0 && nl < Q) {
+        PL = A;
+        A = Part{0.0, 0.0, 0.0};
+      }
+#pragma unroll 8
+      for (int c = 0; c < C; ++c) add(mine[c]);
+    } else {
+      // some root's last left pole, or the end
+      for (int c = 0; c < min(C, Q - p0); ++c) {
+        if (p0 + c == nl) {
+          PL = A;
+          A = Part{0.0, 0.0, 0.0};
+        }
+        add(mine[c]);
+      }
+    }
+  }
+  (nl == Q ? PL : PR) = A;
 }
 
 // One root's iteration state (one lane).  The start, the origin choice, the
@@ -284,19 +358,20 @@ __device__ inline void count_roots(const Work& w, int node, int N, int iters, in
 // Start of the iteration: 0 the interval midpoint, 1 a caller-given position
 // (w.xs), 2 the network's proposal computed here (w.mlp_pk).
 //
-// Secular roots of one node with more than sec_small_n kept values: 64 roots
-// per workgroup, one per lane; the four wavefronts each sum a quarter of the
-// poles for all 64 roots (staged in LDS, read by every lane at the same
-// address), and wavefront 0 combines the partial sums -- left-pole sums in
+// Secular roots of one node with more than sec_small_n kept values: 64 or 16
+// roots per workgroup; the four wavefronts each sum a quarter of the poles for
+// all of them, one root per lane (the poles staged in LDS, read by every lane
+// at the same address) or, for at most 16 roots, with sum_shared, and wavefront 0 combines the partial sums -- left-pole sums in
 // ascending quarter order, right-pole sums in descending order, so both stay
 // summed from far to near -- and advances each root's iteration.
 template <int kMode>
 struct WideLds {
   SecLds<kMode> L;
   float s_x[kSecRoots];
-  double part[kSecWaves][5][kSecRoots];
+  __attribute__((aligned(16))) double part[kSecWaves][5][kSecRoots];
   double b_ov[kSecRoots], b_tau[kSecRoots];
   int b_need[kSecRoots];
+  int b_idx[kSecRoots];
   int b_go;
 };
 
@@ -308,7 +383,11 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
   double* b_ov = S.b_ov;
   double* b_tau = S.b_tau;
   int* b_need = S.b_need;
+  int* b_idx = S.b_idx;
   int& b_go = S.b_go;
+  static_assert(sizeof(part[0]) >= 16 * kSecFew * (2 * 64 / kSecFew + 1) && sizeof(part[0]) >= 16 * 4 * 33 &&
+                    sizeof(part[0]) % 16 == 0,
+                "a wavefront's partial sums give way to its terms");
   const double rho = w.st[nd.id].rho;
   const int64_t vo = nd.vec_off + nd.r0;
   const double* __restrict__ d = w.sd + vo;
@@ -326,7 +405,10 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
   const int Q = (N + kSecWaves - 1) / kSecWaves;
   const int q0 = min(N, wv * Q), q1 = min(N, q0 + Q);
   const bool resident = (q1 - q0) <= kSecChunk;  // the quarter fits in LDS once
-  const bool run = (int)blockIdx.y * kSecRoots < N;
+  // roots per workgroup: few enough to share the terms from the first round on
+  // where the launch has workgroups for it
+  const int G = N <= ny * kSecFew ? kSecFew : kSecRoots;
+  const bool run = (int)blockIdx.y * G < N;
 
   if (kMode != 2 && resident && run) {
     for (int j = q0 + lane; j < q1; j += 64) {
@@ -334,11 +416,11 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
       cz[wv][j - q0] = z[j] * z[j];
     }
   }
-  for (int base = blockIdx.y * kSecRoots; base < N; base += ny * kSecRoots) {
+  for (int base = blockIdx.y * G; base < N; base += ny * G) {
     if constexpr (kMode == 2) {
-      // the network's proposals for roots base .. base+63, then the poles
+      // the network's proposals for the workgroup's roots, then the poles
       __syncthreads();
-      if (net) learned_proposals(w, L.m, d, z, N, rho, base, s_x, kRows);
+      if (net) learned_proposals(w, L.m, d, z, N, rho, base, s_x, G);
       if (resident)
         for (int j = q0 + lane; j < q1; j += 64) {
           cd[wv][j - q0] = d[j];
@@ -346,20 +428,59 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
         }
     }
     const int i = base + lane;
-    const bool active = i < N;
+    const bool active = lane < G && i < N;
     Root R;
-    const float xp = net ? s_x[lane] : (kMode == 1 && active ? w.xs[vo + i] : 0.0f);
+    const float xp = net && active ? s_x[lane] : (kMode == 1 && active ? w.xs[vo + i] : 0.0f);
     R.init(d, N, rho, N == 1 ? z[0] : 0.0, i, active, learned, xp);
     for (;;) {
       if (wv == 0) {
         b_ov[lane] = R.ov;
         b_tau[lane] = R.tau;
         b_need[lane] = R.need ? 1 : 0;
-        const int any = __any(R.need) ? 1 : 0;
-        if (lane == 0) b_go = any;
+        const unsigned long long left = __ballot(R.need);
+        if (R.need) b_idx[__popcll(left & ((1ull << lane) - 1ull))] = lane;
+        if (lane == 0) b_go = __popcll(left);
       }
       __syncthreads();
-      if (!b_go) break;
+      const int go = __builtin_amdgcn_readfirstlane(b_go);
+      if (go == 0) break;
+      if (go <= kSecFew) {
+        // few roots left: their terms shared among the lanes
+        auto shared = [&](auto few) {
+          constexpr int RP = decltype(few)::value;
+          const int slot = lane / (64 / RP);
+          const int k = b_idx[slot < go ? slot : 0];
+          const double eov = b_ov[k], etau = b_tau[k];
+          const int elp = base + k == N - 1 ? N - 2 : base + k;
+          double2* buf = reinterpret_cast<double2*>(&part[wv][0][0]);
+          Part PL{0.0, 0.0, 0.0}, PR{0.0, 0.0, 0.0};
+          if (resident)
+            sum_shared<RP>(buf, q0, q1, elp, eov, etau,
+                           [&](int j, double& dd, double& zz) {
+                             dd = cd[wv][j - q0];
+                             zz = cz[wv][j - q0];
+                           },
+                           PL, PR);
+          else
+            sum_shared<RP>(buf, q0, q1, elp, eov, etau,
+                           [&](int j, double& dd, double& zz) {
+                             dd = d[j];
+                             zz = z[j] * z[j];
+                           },
+                           PL, PR);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          if (slot < go && lane % (64 / RP) == 0) {
+            part[wv][0][k] = PL.s;
+            part[wv][1][k] = PL.ds;
+            part[wv][2][k] = PR.s;
+            part[wv][3][k] = PR.ds;
+            part[wv][4][k] = PL.E + PR.E;
+          }
+        };
+        if (go <= 4) shared(std::integral_constant<int, 4>{});
+        else shared(std::integral_constant<int, kSecFew>{});
+      } else {
       // ---- partial sums of this wavefront's quarter
       const bool nd_l = b_need[lane] != 0;
       const double eov = b_ov[lane], etau = b_tau[lane];
@@ -406,6 +527,7 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
       part[wv][2][lane] = PR.s;
       part[wv][3][lane] = PR.ds;
       part[wv][4][lane] = PL.E + PR.E;
+      }
       __syncthreads();
       if (wv == 0 && R.need) {
         double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0, E = 0.0;
@@ -571,8 +693,10 @@ __device__ inline bool columns_part(const NodeDesc& nd, const Work& w, const Sec
 // One launch per level: a node with at most sec_small_n (<= kLanesMaxN) kept
 // values is solved by the lanes-per-root body, a larger one by the wide body;
 // the two share the workgroup's LDS.
+// (At most 168 registers: the LDS holds three workgroups.)
+
 template <int kMode, int L>
-__global__ __launch_bounds__(256) void k_secular(const NodeDesc* __restrict__ nodes, Work w, SecularSplit split) {
+__global__ __launch_bounds__(256, 3) void k_secular(const NodeDesc* __restrict__ nodes, Work w, SecularSplit split) {
   __shared__ union {
     WideLds<kMode> wide;
     LanesLds<kMode, L> lanes;
@@ -752,7 +876,15 @@ void launch_secular(const NodeDesc* nodes, int nnodes, int max_m, bool columns, 
   const bool l8 = max_m <= 64;
   const int small_max = std::min(std::min(w.sec_small_n, kLanesMaxN), max_m);
   const int ys = (small_max + (l8 ? 32 : 16) - 1) / (l8 ? 32 : 16);
-  const int yw = max_m > small_max ? (max_m + kSecRoots - 1) / kSecRoots : 0;
+  // 16 roots per workgroup, which share their terms from the first round on
+  // (50 cycles a term for the 16), while a level's workgroups are at most two
+  // per CU; else 64, a lane each (85 cycles a term for the 64) until at most 16
+  // are left.  n = 6000 with nothing deflated, 4513 roots last, of which the
+  // slowest takes 25 rounds and the mean 4.9: 71 workgroups of 64 roots with a
+  // lane each to the end 1.05 ms at the last merge and 2.3 in all, 283 of 16
+  // 0.6 and 1.5; the 2000-problem batch (64) 20.6 -> 20.4 ms.
+  const int few = (max_m + kSecFew - 1) / kSecFew;
+  const int yw = max_m > small_max ? (few * nnodes <= 512 ? few : (max_m + kSecRoots - 1) / kSecRoots) : 0;
   const int gy = grid_y(nnodes, std::max(ys, yw), 4096 + nnodes * ys);
   SecularSplit split{gy, 0};
   int ngather = 0;

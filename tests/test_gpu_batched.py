@@ -234,6 +234,28 @@ def test_columns_in_the_secular_launch(gpu, n, kind):
     assert float((VT @ VT.T - eye).abs().max()) <= 1e-13 * n ** 0.5
 
 
+@pytest.mark.parametrize("n,copies", [(300, 30), (700, 16), (1300, 8), (2600, 4)])
+def test_roots_per_workgroup_do_not_matter(gpu, n, copies):
+    """A problem alone (16 roots of its large merges per workgroup, all rounds
+    with shared terms) and in a batch of copies (64, a lane each until few are
+    left) gives the same bits."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    d, e = inputs.near_ones(n, n)
+    s = Solver(0)
+    try:
+        one = [x.clone() for x in s.svd(torch.from_numpy(d).cuda(), torch.from_numpy(e).cuda())]
+        dd = torch.from_numpy(np.tile(d, copies)).cuda()
+        ee = torch.from_numpy(np.tile(np.append(e, 0.0), copies)).cuda()
+        sig, U, VT = s.svd_batched([n] * copies, dd, ee)
+        for i in range(copies):
+            assert torch.equal(sig[i * n:(i + 1) * n], one[0])
+            assert torch.equal(U[i * n * n:(i + 1) * n * n].view(n, n).T, one[1])
+            assert torch.equal(VT[i * n * n:(i + 1) * n * n].view(n, n).T, one[2])
+    finally:
+        s.close()
+
+
 def test_autotune_picks_a_valid_tuning(gpu):
     import torch
     from paper_2508_11467_amd.api import Solver

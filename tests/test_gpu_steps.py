@@ -352,6 +352,31 @@ def test_secular_matches_oracle(solver, solver_lanes, kernel, N, seed):
         assert abs(np.mean(it) - np.mean(rit)) <= 0.5
 
 
+@pytest.mark.parametrize("N,seed", [(4, 20), (5, 21), (15, 22), (16, 23), (17, 24), (31, 25), (66, 26), (127, 27),
+                                    (511, 28), (2047, 29), (2049, 30), (2052, 31), (8200, 32)])
+def test_secular_shared_terms(solver, N, seed):
+    """The wide body where few roots share their terms' reciprocals: quarters
+    of 0 to 4 poles, of whole and cut steps of 8 and 32 terms, at the end of
+    the poles LDS holds (512 per wavefront), and past 8192 values, where 64
+    roots take a lane each until few are left."""
+    d, z = _arrow(N, seed)
+    keep = solver.tuning()
+    solver.set_tuning(small_n=96, flat=0, grid64=1024, grid128=512, sec_small_n=0)
+    try:
+        o, tau, it = solver.step_secular(d, z)
+    finally:
+        solver.set_tuning(**{k: keep[k] for k in ("small_n", "flat", "grid64", "grid128", "sec_small_n")})
+    o, tau, it = o.cpu().numpy(), tau.cpu().numpy(), it.cpu().numpy()
+    assert np.all(it >= 1) and np.all(it <= 64)
+    w = d[o] + tau
+    assert np.all(np.diff(w) >= 0) and np.all(w[:-1] >= d[:-1]) and np.all(w[:-1] <= d[1:])
+    rows = np.unique(np.r_[np.arange(min(N, 40)), np.linspace(0, N - 1, 200).astype(int)])
+    LD = np.longdouble
+    for i in rows:
+        t = z.astype(LD) ** 2 / ((d.astype(LD) - d[o[i]] - LD(tau[i])) * (d.astype(LD) + d[o[i]] + LD(tau[i])))
+        assert abs(1 + np.sum(t)) <= 32 * 2.0 ** -52 * (1 + np.sum(np.abs(t))), i
+
+
 # ---------------------------------------------------------------- Loewner + vectors
 @pytest.mark.parametrize("N,seed", [(1, 0), (2, 1), (7, 2), (200, 3), (1500, 4)])
 def test_vectors_match_oracle(solver, N, seed):
