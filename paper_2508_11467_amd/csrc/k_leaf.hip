@@ -73,31 +73,43 @@ __device__ inline void rot_cols(double* A, int ld, int rows, int i, int j, doubl
   }
 }
 
+// lane i's value from lane i + 1 / i - 1 (0 past the ends)
+template <int CTRL>
+__device__ inline double wave_shift(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double from_above(double v) { return wave_shift<0x130>(v); }  // wave_shl:1
+__device__ inline double from_below(double v) { return wave_shift<0x138>(v); }  // wave_shr:1
+
 __device__ inline double wave_max(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
   return v;
 }
 
 // Two wavefronts per leaf.  Wavefront 0 runs the Givens chain of a sweep and
-// leaves its rotations in LDS; wavefront 1 does the rest: the tests before a
-// sweep (lane i holds d_i and e_i, the superdiagonal entry right of d_i), the
-// shift, the rare rotations that are no sweep, and, while the next sweep's
-// chain runs, the last sweep's rotations of W and Q (lane r: row r of the
-// column-major LDS copies; the column being rotated forward stays in a
-// register).
+// leaves its rotations' arguments in LDS; wavefront 1 does the rest: the
+// rotations from their arguments (lane k: step k), the tests before a sweep
+// (lane i holds d_i and e_i, the superdiagonal entry right of d_i), the shift
+// (lane i: were the block to end at i, so that it does not wait for the tests),
+// the rare rotations that are no sweep, and, while the next sweep's chain runs,
+// the last sweep's rotations of W and Q (lane r: row r of the column-major LDS
+// copies; the column being rotated forward stays in a register).
 //
-// The chain bounds the time: 38 FP64 operations and two reciprocal square
+// The chain bounds the time: 35 FP64 operations and two reciprocal square
 // roots a step, about 1150 steps for a 32-row leaf, on one wavefront.  So it
 // holds nothing else: no test (each step's rotations take givens()' usual
 // path; a rotation that would not have shows afterwards by s = 0 or a tiny r,
-// and wavefront 1 redoes such a sweep step by step), no cross-lane read, and
-// no update of W or Q.  Measured (leaves of 16..32 rows): the leaves of n =
-// 100 155 us, of n = 1000 237 and of n = 16384 280, against 260, 443 and 555
-// for one wavefront doing everything with a test per rotation (about 345
-// against 900 cycles a step); 40000 leaves of a batch, which fill the chip
-// either way, 4.8 against 6.2 ms.  Several leaves per chain wavefront (a lane
-// each) measured slower in both regimes (322-369 us and 6.2-8 ms): lanes wait
-// for the longest block.
+// and wavefront 1 redoes such a sweep step by step), no cross-lane read, no
+// update of W or Q, and as few LDS writes as the rotations can be had from
+// (25 cycles each).  Measured (leaves of 16..32 rows): the leaves of n = 100
+// 132 us, of n = 1000 212 and of n = 16384 247; 155, 237 and 280 with (c, s) and
+// the new entries posted and the shift after the tests; 260, 443 and 555 for
+// one wavefront doing everything with a test per rotation; 40000 leaves of a
+// batch, which fill the chip either way, 4.2, 4.8 and 6.2 ms.  Several leaves
+// per chain wavefront (a lane each) measured slower in both regimes (322-369 us
+// and 6.2-8 ms): lanes wait for the longest block.
 template <int ML>
 struct LeafLds {
   static constexpr int kLd = ML + 1;  // column stride (doubles)
@@ -105,12 +117,14 @@ struct LeafLds {
   double Q[(ML + 1) * kLd];
   struct Sweep {            // one posted sweep, by parity
     double2 in[ML + 2];     // (d_i, e_i) before it
-    double2 out[ML + 2];    // (d_i, e_{i-1}) after it
-    double2 rq[ML + 2];     // (c, s) of the rotation of Q's (W's) columns (k, k+1),
+    double2 yz[ML + 2];     // step k: the arguments of the rotation of Q's columns (k, k+1)
+    double2 nd[ML + 2];     // and (x) the first one of W's, whose second is s d_{k+1}
+    double2 rq[ML + 2];     // (c, s) of the two rotations
     double2 rw[ML + 2];
+    double2 last;           // (d_hi, e_{hi-1}) after it
   } sw[2];
   double2 yz;               // the first rotation's two entries
-  int lo, hi;               // the sweep's block; hi = 0: no more sweeps
+  int2 block;               // the sweep's block (lo, hi); hi = 0: no more sweeps
 };
 
 // one sweep's chain on the entries of `in`: steps lo .. lo + n - 1
@@ -129,9 +143,8 @@ __device__ inline void leaf_chain(typename LeafLds<ML>::Sweep& S, int lo, int n,
     const double nek = fma(c, ek, -(s * dk));
     const double ndk1 = c * dk1;
     givens_fast(ndk, bulge, c2, s2, r2);
-    p->rq[0] = make_double2(c, s);
-    p->out[0] = make_double2(r2, r);
-    p->rw[0] = make_double2(c2, s2);
+    p->yz[0] = make_double2(y, z);
+    p->nd[0].x = ndk;
     y = fma(nek, c2, ndk1 * s2);      // e_k
     dk = fma(ndk1, c2, -(nek * s2));  // d_{k+1}
     z = s2 * ek1;                     // the bulge right of e_k
@@ -140,7 +153,7 @@ __device__ inline void leaf_chain(typename LeafLds<ML>::Sweep& S, int lo, int n,
     ek1 = v2.y;
     p = reinterpret_cast<typename LeafLds<ML>::Sweep*>(reinterpret_cast<double2*>(p) + 1);
   }
-  p->out[0] = make_double2(dk, y);
+  S.last = make_double2(dk, y);
 }
 
 // the rotations of one sweep on row `lane` of W and Q
@@ -162,6 +175,25 @@ __device__ inline void leaf_apply(LeafLds<ML>& S, const typename LeafLds<ML>::Sw
   w[hi * kLd] = wk;
 }
 
+// The same for leaves of at most 32 columns: lanes 0..31 have Q's rows, lanes
+// 32..63 W's, so that a step is half the instructions (a batch's leaves 4.38 ->
+// 4.23 ms; hidden behind the chain otherwise).
+template <int ML>
+__device__ inline void leaf_apply_halves(LeafLds<ML>& S, const typename LeafLds<ML>::Sweep& R, int lo, int hi,
+                                         int lane) {
+  constexpr int kLd = LeafLds<ML>::kLd;
+  double* x = (lane < 32 ? S.Q : S.W) + (lane & 31);
+  const double2* rot = lane < 32 ? R.rq : R.rw;
+  double xk = x[lo * kLd];
+  for (int k = lo; k < hi; ++k) {
+    const double2 a = rot[k];
+    const double xk1 = x[(k + 1) * kLd];
+    x[k * kLd] = fma(xk, a.x, a.y * xk1);
+    xk = fma(xk1, a.x, -(xk * a.y));
+  }
+  x[hi * kLd] = xk;
+}
+
 template <int ML>
 __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leaves, Work w) {
   constexpr int kLd = LeafLds<ML>::kLd;
@@ -173,9 +205,9 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
   if (threadIdx.x < 64) {
     for (int par = 0;; par ^= 1) {
       __syncthreads();
-      const int lo = __builtin_amdgcn_readfirstlane(S.lo), hi = __builtin_amdgcn_readfirstlane(S.hi);
-      if (hi == 0) return;
       const double2 yz = S.yz;
+      const int lo = __builtin_amdgcn_readfirstlane(S.block.x), hi = __builtin_amdgcn_readfirstlane(S.block.y);
+      if (hi == 0) return;
       if (lane == 0) leaf_chain<ML>(S.sw[par], lo, hi - lo, yz.x, yz.y);
       __syncthreads();
     }
@@ -237,42 +269,62 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
   double mu = 0.0;
   bool go = false, pending = false;  // a sweep posted for this parity; the last sweep's rotations not applied yet
   int phi = 0, plo = 0;
+  double c = 0.0, sn = 0.0, c2 = 0.0, sn2 = 0.0;  // step lane's rotations of the last sweep
+  auto apply = [&](int par) {
+    typename LeafLds<ML>::Sweep& R = S.sw[par];
+    if (lane <= ML) {
+      R.rq[lane] = make_double2(c, sn);
+      R.rw[lane] = make_double2(c2, sn2);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (ms <= 32) {
+      if ((lane & 31) < ms) leaf_apply_halves<ML>(S, R, plo, phi, lane);
+    } else if (row) {
+      leaf_apply<ML>(S, R, plo, phi, lane);
+    }
+  };
   for (int par = 0;; par ^= 1) {
     // the posted sweep's outcome, then the tests before the next one
     if (go) {
       const typename LeafLds<ML>::Sweep& R = S.sw[par ^ 1];
-      const double2 o0 = R.out[lane <= ML ? lane : 0], o1 = R.out[lane <= ML ? lane + 1 : 0];
-      const double sq = R.rq[lane <= ML ? lane : 0].y, sw = R.rw[lane <= ML ? lane : 0].y;
+      const int at = lane <= ML ? lane : 0;
+      const double2 yz = R.yz[at], last = R.last;
+      double r, r2;
+      givens_fast(yz.x, yz.y, c, sn, r);
+      givens_fast(R.nd[at].x, sn * R.in[at + 1].x, c2, sn2, r2);
       // s = 0 where g = 0 (or g / r underflowed); r < 2^-470 well before f^2 + g^2 <= 2^-960
-      const bool odd = lane >= lo && lane < hi && (sq == 0.0 || sw == 0.0 || !(o0.x > 0x1p-470) || !(o0.y > 0x1p-470));
+      const bool odd = lane >= lo && lane < hi && (sn == 0.0 || sn2 == 0.0 || !(r2 > 0x1p-470) || !(r > 0x1p-470));
+      const double rn = from_above(r);
       if (__any(odd) || bad) {
         // again from the entries as posted, every rotation by givens()
         double dk = lane_val(dreg, lo), ek = lane_val(ereg, lo);
         double y = fma(dk, dk, -mu), z = dk * ek;
         for (int k = lo; k < hi; ++k) {
           const double dk1 = lane_val(dreg, k + 1), ek1 = k < hi - 1 ? lane_val(ereg, k + 1) : 0.0;
-          double c, sn, r, c2, sn2, r2;
-          givens(y, z, c, sn, r);
-          if (k > lo && lane == k - 1) ereg = r;
-          const double ndk = fma(c, dk, sn * ek);
-          const double nek = fma(c, ek, -(sn * dk));
-          const double ndk1 = c * dk1;
-          givens(ndk, sn * dk1, c2, sn2, r2);
-          if (lane == k) dreg = r2;
-          if (lane == 0) {
-            S.sw[par ^ 1].rq[k] = make_double2(c, sn);
-            S.sw[par ^ 1].rw[k] = make_double2(c2, sn2);
+          double kc, ks, kr, kc2, ks2, kr2;
+          givens(y, z, kc, ks, kr);
+          if (k > lo && lane == k - 1) ereg = kr;
+          const double ndk = fma(kc, dk, ks * ek);
+          const double nek = fma(kc, ek, -(ks * dk));
+          const double ndk1 = kc * dk1;
+          givens(ndk, ks * dk1, kc2, ks2, kr2);
+          if (lane == k) {
+            dreg = kr2;
+            c = kc;
+            sn = ks;
+            c2 = kc2;
+            sn2 = ks2;
           }
-          y = fma(nek, c2, ndk1 * sn2);
-          dk = fma(ndk1, c2, -(nek * sn2));
-          z = sn2 * ek1;
-          ek = c2 * ek1;
+          y = fma(nek, kc2, ndk1 * ks2);
+          dk = fma(ndk1, kc2, -(nek * ks2));
+          z = ks2 * ek1;
+          ek = kc2 * ek1;
         }
         if (lane == hi - 1) ereg = y;
         if (lane == hi) dreg = dk;
       } else {
-        if (lane >= lo && lane <= hi) dreg = o0.x;
-        if (lane >= lo && lane < hi) ereg = o1.y;
+        if (lane >= lo && lane <= hi) dreg = lane == hi ? last.x : r2;
+        if (lane >= lo && lane < hi) ereg = lane == hi - 1 ? last.y : rn;
       }
       nrot_q += hi - lo;
       nrot_w += hi - lo;
@@ -281,11 +333,25 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
       phi = hi;
       go = false;
     }
+    double mul = 0.0;
     while (hi > 0) {
       // negligible superdiagonals -> 0; then the unreduced block [lo, hi]
-      const double dnext = __shfl_down(dreg, 1, 64);
+      const double dnext = from_above(dreg);
       if (lane < hi && fabs(ereg) <= kEps * (fabs(dreg) + fabs(dnext))) ereg = 0.0;
       const unsigned long long nz = __ballot(lane < hi && ereg != 0.0);
+      {
+        // Wilkinson shift were the block to end at this lane: eigenvalue of the
+        // trailing 2x2 of B^T B nearer its end (for a block of two, the entry
+        // before it is zero)
+        const double dm = from_below(dreg), dn = dreg, fm = from_below(ereg);
+        const double g = from_below(fm);
+        const double t11 = dm * dm + g * g, t12 = dm * fm, t22 = dn * dn + fm * fm;
+        const double delta = 0.5 * (t11 - t22);
+        const double root = hypot(delta, t12);
+        const double denom = delta + (delta >= 0.0 ? root : -root);
+        mul = t12 == 0.0 ? t22 : t22 - t12 * t12 / denom;
+        asm volatile("" : "+v"(mul));  // here, beside the tests' waits
+      }
       hi = nz ? 64 - __builtin_clzll(nz) : 0;
       if (hi == 0) break;
       if (steps >= max_steps) {
@@ -301,7 +367,7 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
         go = true;
         break;
       }
-      if (pending && row) leaf_apply<ML>(S, S.sw[par ^ 1], plo, phi, lane);
+      if (pending) apply(par ^ 1);
       pending = false;
       const int i = __builtin_ctzll(zd);
       if (lane == i) dreg = 0.0;
@@ -310,15 +376,15 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
         double f = lane_val(ereg, i);
         if (lane == i) ereg = 0.0;
         for (int j = i + 1; j <= hi; ++j) {
-          double c, sn, r;
-          givens(lane_val(dreg, j), f, c, sn, r);
-          if (lane == j) dreg = r;
+          double kc, ks, kr;
+          givens(lane_val(dreg, j), f, kc, ks, kr);
+          if (lane == j) dreg = kr;
           if (j < hi) {
             const double t = lane_val(ereg, j);
-            f = -sn * t;
-            if (lane == j) ereg = c * t;
+            f = -ks * t;
+            if (lane == j) ereg = kc * t;
           }
-          rot_cols(W, kLd, m, j, i, c, sn, lane);
+          rot_cols(W, kLd, m, j, i, kc, ks, lane);
           ++nrot_w;
         }
       } else {
@@ -326,42 +392,27 @@ __global__ __launch_bounds__(128) void k_leaf(const LeafDesc* __restrict__ leave
         double f = lane_val(ereg, hi - 1);
         if (lane == hi - 1) ereg = 0.0;
         for (int j = hi - 1; j >= lo; --j) {
-          double c, sn, r;
-          givens(lane_val(dreg, j), f, c, sn, r);
-          if (lane == j) dreg = r;
+          double kc, ks, kr;
+          givens(lane_val(dreg, j), f, kc, ks, kr);
+          if (lane == j) dreg = kr;
           if (j > lo) {
             const double t = lane_val(ereg, j - 1);
-            f = -sn * t;
-            if (lane == j - 1) ereg = c * t;
+            f = -ks * t;
+            if (lane == j - 1) ereg = kc * t;
           }
-          rot_cols(Q, kLd, ms, j, hi, c, sn, lane);
+          rot_cols(Q, kLd, ms, j, hi, kc, ks, lane);
           ++nrot_q;
         }
       }
     }
     if (go) {
-      // Wilkinson shift: eigenvalue of the trailing 2x2 of B^T B nearer its end
-      const double dm = lane_val(dreg, hi - 1), dn = lane_val(dreg, hi), fm = lane_val(ereg, hi - 1);
-      const double g = (hi - 1 > lo) ? lane_val(ereg, hi - 2) : 0.0;
-      const double t11 = dm * dm + g * g, t12 = dm * fm, t22 = dn * dn + fm * fm;
-      if (t12 == 0.0) {
-        mu = t22;
-      } else {
-        const double delta = 0.5 * (t11 - t22);
-        const double root = hypot(delta, t12);
-        const double denom = delta + (delta >= 0.0 ? root : -root);
-        mu = t22 - t12 * t12 / denom;
-      }
+      mu = lane_val(mul, hi);
       if (lane <= ML) S.sw[par].in[lane] = make_double2(dreg, ereg);
-      const double dk = lane_val(dreg, lo);
-      if (lane == 0) S.yz = make_double2(fma(dk, dk, -mu), dk * lane_val(ereg, lo));
+      if (lane == lo) S.yz = make_double2(fma(dreg, dreg, -mu), dreg * ereg);
     }
-    if (lane == 0) {
-      S.lo = lo;
-      S.hi = go ? hi : 0;
-    }
+    if (lane == 0) S.block = make_int2(lo, go ? hi : 0);
     __syncthreads();
-    if (pending && row) leaf_apply<ML>(S, S.sw[par ^ 1], plo, phi, lane);
+    if (pending) apply(par ^ 1);
     pending = false;
     if (!go) break;
     __syncthreads();

@@ -96,6 +96,28 @@ def test_leaf_lds_classes(solver, m, s):
         assert np.max(np.abs(Q.T @ Q - np.eye(m + s))) <= 1e-14
 
 
+@pytest.mark.parametrize("m,s", [(2, 0), (2, 1), (30, 1), (31, 0), (31, 1), (32, 0), (32, 1)])
+@pytest.mark.parametrize("low", [1.0, 1e-8, 1e-150])
+def test_leaf_widest(solver, m, s, low):
+    """At most 32 columns (rows of both factors side by side in a wavefront)
+    and 33; blocks of two; a lower half so small that its rotations leave the
+    usual path (f^2 + g^2 under 2^-960) and are redone."""
+    g = np.random.default_rng(7 * m + s)
+    d = g.uniform(0.5, 1, m) * np.where(np.arange(m) < m // 2, 1.0, low)
+    e = g.uniform(0.5, 1, m - 1 + s) * np.where(np.arange(m - 1 + s) < m // 2 - 1, 1.0, low)
+    if m // 2 - 1 >= 0:
+        e[m // 2 - 1] = 0.0
+    sig, W, Q = (x.cpu().numpy() for x in solver.step_leaf(d, e, s))
+    ref, _, _, _ = oracle.leaf_svd(d, e, s)
+    B = obdc.dense_bidiagonal(d, e, s)
+    S = np.zeros((m, m + s))
+    S[np.arange(m), np.arange(m)] = sig
+    assert np.max(np.abs(sig - ref)) <= 1e-14 * ref[-1]
+    assert np.linalg.norm(B - W @ S @ Q.T) <= 1e-14 * np.linalg.norm(B)
+    assert np.max(np.abs(W.T @ W - np.eye(m))) <= 1e-14
+    assert np.max(np.abs(Q.T @ Q - np.eye(m + s))) <= 1e-14
+
+
 @pytest.mark.parametrize("case", ["zero_diag_mid", "zero_diag_last", "zero_e", "all_zero", "graded", "huge", "tiny"])
 def test_leaf_special(solver, case):
     m, s = 20, 1
