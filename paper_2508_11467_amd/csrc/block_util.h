@@ -3,13 +3,61 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace bdc {
 
 constexpr int kBlock = 256;
 
+// v combined over the wavefront in the order of lane distances 32, 16, 8, 4, 2
+// and 1, in all lanes (op commutative).  Half-wavefront and row swaps, then row
+// rotations (after the distance of 8 a row repeats every 8 lanes, and so on, so
+// a rotation meets the same partner): no LDS round trips, which made up most of
+// the small merges' reductions (a shuffle of a double is 57 cycles).
+template <class Op>
+__device__ __forceinline__ double half_wave_all(double v, Op op) {  // from the distance of 16 on
+  auto swap16 = [&](double x) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+    return op(__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1]));
+  };
+  auto rotate = [&](double x, auto ctrl) {
+    constexpr int c = decltype(ctrl)::value;
+    return op(x, __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), c, 0xF, 0xF, false),
+                                  __builtin_amdgcn_update_dpp(0, __double2loint(x), c, 0xF, 0xF, false)));
+  };
+  v = swap16(v);
+  v = rotate(v, std::integral_constant<int, 0x128>{});  // row_ror:8
+  v = rotate(v, std::integral_constant<int, 0x124>{});
+  v = rotate(v, std::integral_constant<int, 0x122>{});
+  return rotate(v, std::integral_constant<int, 0x121>{});
+}
+
+// x of the lower half of the wavefront and of the upper half, in both halves
+struct Halves {
+  double lower, upper;
+};
+__device__ __forceinline__ Halves wave_halves(double x) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+  return Halves{__hiloint2double(hi[0], lo[0]), __hiloint2double(hi[1], lo[1])};
+}
+
+template <class Op>
+__device__ __forceinline__ double wave_all(double v, Op op) {
+  const Halves h = wave_halves(v);
+  return half_wave_all(op(h.lower, h.upper), op);
+}
+
+// sum of the lanes' squares, a lane's own square unrounded where it meets the
+// other half's
+__device__ __forceinline__ double wave_sum_squares(double v) {
+  const Halves h = wave_halves(v * v);
+  return half_wave_all(fma(v, v, (threadIdx.x & 32) ? h.lower : h.upper), [](double a, double b) { return a + b; });
+}
+
 __device__ inline double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  return wave_all(v, [](double a, double b) { return a + b; });
 }
 
 // x plus lane-shifted x's by DPP (no LDS round trip): a shift or broadcast
@@ -40,13 +88,11 @@ __device__ __forceinline__ double wave_sum_last(double x) {
 }
 
 __device__ inline double wave_maxd(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
+  return wave_all(v, [](double a, double b) { return fmax(a, b); });
 }
 
 __device__ inline double wave_prod(double v) {
-  for (int off = 32; off > 0; off >>= 1) v *= __shfl_xor(v, off, 64);
-  return v;
+  return wave_all(v, [](double a, double b) { return a * b; });
 }
 
 // All threads of the 256-thread block get the block maximum.

