@@ -567,27 +567,33 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
 // same iteration state.  A wavefront holds 64/L roots, so it iterates only as
 // long as the slowest of those few.
 constexpr int kLanesMaxN = kSecLanesMaxN;
+constexpr int64_t kSecMany = 131072;  // positions of a level from which four lanes take a root
 // The lanes-per-root kernel's network: at most 32 rows (its roots per
 // workgroup) and, for N <= kLanesMaxN = 256, at most 16 far-field blocks.
 struct SmallMlp {
   MlpSharedT<32, 16> m;
 };
 
-// v summed over the aligned group of L lanes (L in {8, 16}; within a DPP row)
-template <int L>
-__device__ inline double group_sum(double v) {
-  static_assert(L == 8 || L == 16, "lanes per root");
+// The sum of L partial sums (8 or 16), T of them in each of L / T consecutive
+// lanes: pairs, quads, halves, whole, whichever lanes hold them.
+template <int L, int T>
+__device__ inline double group_sum(const double (&v)[T]) {
+  static_assert((L == 8 || L == 16) && (T == 1 || L / T == 4), "lanes per root");
   auto step = [](double x, auto ctrl) -> double {
     constexpr int c = decltype(ctrl)::value;
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), c, 0xF, 0xF, false);
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), c, 0xF, 0xF, false);
     return x + __hiloint2double(hi, lo);
   };
-  v = step(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]: lane ^ 1
-  v = step(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]: lane ^ 2
-  v = step(v, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other quad of 8
-  if constexpr (L == 16) v = step(v, std::integral_constant<int, 0x140>{});  // row_mirror
-  return v;
+  double x;
+  if constexpr (T == 4) x = (v[0] + v[1]) + (v[2] + v[3]);
+  else if constexpr (T == 2) x = v[0] + v[1];
+  else x = v[0];
+  x = step(x, std::integral_constant<int, 0xB1>{});  // quad_perm [1,0,3,2]: lane ^ 1
+  x = step(x, std::integral_constant<int, 0x4E>{});  // quad_perm [2,3,0,1]: lane ^ 2
+  if constexpr (T == 1) x = step(x, std::integral_constant<int, 0x141>{});  // row_half_mirror: the other quad of 8
+  if constexpr (T == 1 && L == 16) x = step(x, std::integral_constant<int, 0x140>{});  // row_mirror
+  return x;
 }
 
 template <int kMode, int L>
@@ -597,9 +603,11 @@ struct LanesLds {
   typename std::conditional<kMode == 2, SmallMlp, char>::type M;
 };
 
-template <int kMode, int L>
+template <int kMode, int L, int T>
 __device__ void secular_lanes(const NodeDesc& nd, int N, const Work& w, LanesLds<kMode, L>& S) {
-  constexpr int kRoots = 256 / L;
+  constexpr int P = L / T;  // lanes per root, T of the L partial sums in each
+  constexpr int kRoots = 256 / P;
+  static_assert(T == 1 || kMode != 2, "the network's rows");
   double* cd = S.cd;
   double* cz = S.cz;
   float* s_x = S.s_x;
@@ -629,8 +637,8 @@ __device__ void secular_lanes(const NodeDesc& nd, int N, const Work& w, LanesLds
     cz[j] = j < N ? z[j] * z[j] : 0.0;
   }
   __syncthreads();
-  const int part = t & (L - 1);
-  const int i = base + t / L;
+  const int part = t & (P - 1);
+  const int i = base + t / P;
   const bool active = i < N;
   Root R;
   const float xp = net ? s_x[i - base] : (kMode == 1 && active ? w.xs[vo + i] : 0.0f);
@@ -638,23 +646,26 @@ __device__ void secular_lanes(const NodeDesc& nd, int N, const Work& w, LanesLds
   while (R.need) {
     // left model poles j <= lp, right ones above (for the last root the
     // right side is the last pole alone, below the root like the others)
-    double sL = 0.0, sR = 0.0, dL = 0.0, dR = 0.0;
+    double sL4[T], sR4[T], dL4[T], dR4[T];
+#pragma unroll
+    for (int u = 0; u < T; ++u) sL4[u] = sR4[u] = dL4[u] = dR4[u] = 0.0;
     for (int q = 0; q < steps; ++q) {
-      const int j = part + q * L;
-      const double dd = cd[j];
-      const double del = ((dd - R.ov) - R.tau) * ((dd + R.ov) + R.tau);  // d_j^2 - omega^2
-      const double r = recip(del);
-      const double tj = cz[j] * r;
-      const double tl = j <= R.lp ? tj : 0.0, tg = tj - tl;  // exact split
-      sL += tl;
-      sR += tg;
-      dL = fma(tl, r, dL);
-      dR = fma(tg, r, dR);
+#pragma unroll
+      for (int u = 0; u < T; ++u) {
+        const int j = part * T + u + q * L;
+        const double dd = cd[j];
+        const double del = ((dd - R.ov) - R.tau) * ((dd + R.ov) + R.tau);  // d_j^2 - omega^2
+        const double r = recip(del);
+        const double tj = cz[j] * r;
+        const double tl = j <= R.lp ? tj : 0.0, tg = tj - tl;  // exact split
+        sL4[u] += tl;
+        sR4[u] += tg;
+        dL4[u] = fma(tl, r, dL4[u]);
+        dR4[u] = fma(tg, r, dR4[u]);
+      }
     }
-    sL = group_sum<L>(sL);
-    sR = group_sum<L>(sR);
-    dL = group_sum<L>(dL);
-    dR = group_sum<L>(dR);
+    const double sL = group_sum<L>(sL4), sR = group_sum<L>(sR4);
+    const double dL = group_sum<L>(dL4), dR = group_sum<L>(dR4);
     // left terms are negative and right ones positive (the last root's one
     // right term is negative too): sum |t| = |sR| - sL
     const double f = (1.0 + sL) + sR;
@@ -669,24 +680,19 @@ __device__ void secular_lanes(const NodeDesc& nd, int N, const Work& w, LanesLds
   count_roots(w, nd.id, N, writer ? R.iters : 0, writer ? R.capped : 0);
 }
 
-// The workgroups of a merge past its secular ones (y >= split.ny): first the
-// rotations of its deflated pairs, then the gather of its kept columns.  They
+// The workgroups of a merge past its secular ones (y >= ny) share the
+// rotations of its deflated pairs and the gather of its kept columns.  They
 // and the secular solve need the deflation's lists only, and none reads what
 // another writes, so one launch holds all three: two launches less per level
 // (about 4.5 us each: n = 1000, five levels, 488 -> 443 us; n = 16384 1934 ->
 // 1722), and the columns, bound by memory, move while the roots, bound by
 // arithmetic, are found (the 2000-problem batch 21.7 -> 20.6 ms, n = 6000 with
 // nothing deflated 11.0 -> 10.6).
-struct SecularSplit {
-  int ny;    // secular workgroups per merge
-  int nrot;  // workgroups per merge that rotate; the rest of the grid gathers
-};
-
-__device__ inline bool columns_part(const NodeDesc& nd, const Work& w, const SecularSplit& split) {
-  const int y = (int)blockIdx.y - split.ny;
+__device__ inline bool columns_part(const NodeDesc& nd, const Work& w, int ny) {
+  const int y = (int)blockIdx.y - ny;
   if (y < 0) return false;
-  if (y < split.nrot) rotate_node<true>(nd, w, y, split.nrot);
-  else gather_node<true>(nd, w, y - split.nrot, (int)gridDim.y - split.ny - split.nrot);
+  rotate_node<true>(nd, w, y, (int)gridDim.y - ny);
+  gather_node<true>(nd, w, y, (int)gridDim.y - ny);
   return true;
 }
 
@@ -696,28 +702,27 @@ __device__ inline bool columns_part(const NodeDesc& nd, const Work& w, const Sec
 // (At most 168 registers: the LDS holds three workgroups.)
 
 template <int kMode, int L>
-__global__ __launch_bounds__(256, 3) void k_secular(const NodeDesc* __restrict__ nodes, Work w, SecularSplit split) {
+__global__ __launch_bounds__(256, 3) void k_secular(const NodeDesc* __restrict__ nodes, Work w, int ny) {
   __shared__ union {
     WideLds<kMode> wide;
     LanesLds<kMode, L> lanes;
   } S;
   const NodeDesc nd = nodes[blockIdx.x];
-  if (columns_part(nd, w, split)) return;
+  if (columns_part(nd, w, ny)) return;
   const int N = w.st[nd.id].N;
-  if (N <= w.sec_small_n && N <= kLanesMaxN) secular_lanes<kMode, L>(nd, N, w, S.lanes);
-  else secular_wide<kMode>(nd, N, w, split.ny, S.wide);
+  if (N <= w.sec_small_n && N <= kLanesMaxN) secular_lanes<kMode, L, 1>(nd, N, w, S.lanes);
+  else secular_wide<kMode>(nd, N, w, ny, S.wide);
 }
 
 // Levels whose merges all take the lanes-per-root body (every merge at most
 // sec_small_n <= kLanesMaxN values): the LDS of that body alone, so more
 // workgroups fit on a CU.
-template <int kMode, int L>
-__global__ __launch_bounds__(256) void k_secular_lanes(const NodeDesc* __restrict__ nodes, Work w,
-                                                       SecularSplit split) {
+template <int kMode, int L, int T>
+__global__ __launch_bounds__(256) void k_secular_lanes(const NodeDesc* __restrict__ nodes, Work w, int ny) {
   __shared__ LanesLds<kMode, L> S;
   const NodeDesc nd = nodes[blockIdx.x];
-  if (columns_part(nd, w, split)) return;
-  secular_lanes<kMode, L>(nd, w.st[nd.id].N, w, S);
+  if (columns_part(nd, w, ny)) return;
+  secular_lanes<kMode, L, T>(nd, w.st[nd.id].N, w, S);
 }
 
 __global__ __launch_bounds__(256) void k_lowner(const NodeDesc* __restrict__ nodes, Work w) {
@@ -876,7 +881,17 @@ void launch_secular(const NodeDesc* nodes, int nnodes, int max_m, bool columns, 
   // 8 lanes per root while the merges are at most 64 values, else 16
   const bool l8 = max_m <= 64;
   const int small_max = std::min(std::min(w.sec_small_n, kLanesMaxN), max_m);
-  const int ys = (small_max + (l8 ? 32 : 16) - 1) / (l8 ? 32 : 16);
+  const int mode = w.mlp_pk ? 2 : (w.xs ? 1 : 0);
+  const bool lanes_only = max_m <= small_max;  // every merge has N <= max_m <= small_max
+  // Four lanes per root where a level's roots fill the chip: they hold the L
+  // partial sums of the 8 or 16 lanes between them, so the sums are the same,
+  // and a round's model step, 900 cycles whatever the lanes, serves 16 roots of
+  // a wavefront instead of 8 or 4 (the 2000-problem batch's launches with 8 and
+  // 16, gathers included, 0.93 and 0.82 ms a level, with four 0.82 and 0.66).
+  // Fewer roots finish sooner with more lanes each.
+  const bool many = lanes_only && mode != 2 && (int64_t)nnodes * max_m >= kSecMany;
+  const int roots = many ? 64 : (l8 ? 32 : 16);  // per workgroup
+  const int ys = (small_max + roots - 1) / roots;
   // 16 roots per workgroup, which share their terms from the first round on
   // (50 cycles a term for the 16), while a level's workgroups are at most two
   // per CU; else 64, a lane each (85 cycles a term for the 64) until at most 16
@@ -887,22 +902,20 @@ void launch_secular(const NodeDesc* nodes, int nnodes, int max_m, bool columns, 
   const int few = (max_m + kSecFew - 1) / kSecFew;
   const int yw = max_m > small_max ? (few * nnodes <= 512 ? few : (max_m + kSecRoots - 1) / kSecRoots) : 0;
   const int gy = grid_y(nnodes, std::max(ys, yw), 4096 + nnodes * ys);
-  SecularSplit split{gy, 0};
-  int ngather = 0;
-  if (columns) {
-    split.nrot = grid_y(nnodes, rotate_units(max_m), 4096);
-    // at most 32768 per merge: the grid's second dimension ends at 65535
-    ngather = grid_y(nnodes, (int)std::min<int64_t>(32768, gather_units(max_m)), 65536);
-  }
-  const dim3 grid(nnodes, gy + split.nrot + ngather), block(256);
-  const int mode = w.mlp_pk ? 2 : (w.xs ? 1 : 0);
-  const bool lanes_only = max_m <= small_max;  // every merge has N <= max_m <= small_max
+  // the columns' workgroups: about 32768 in all (with 65536, many of them empty,
+  // a batch's level takes 50 us more), at most 32768 per merge, as the grid's
+  // second dimension ends at 65535
+  const int nc = columns ? grid_y(nnodes, (int)std::min<int64_t>(32768, gather_units(max_m)), 32768) : 0;
+  const dim3 grid(nnodes, gy + nc), block(256);
 #define BDC_LAUNCH_SEC(M)                                                                        \
   do {                                                                                           \
-    if (lanes_only && l8) hipLaunchKernelGGL((k_secular_lanes<M, 8>), grid, block, 0, st, nodes, w, split); \
-    else if (lanes_only) hipLaunchKernelGGL((k_secular_lanes<M, 16>), grid, block, 0, st, nodes, w, split); \
-    else if (l8) hipLaunchKernelGGL((k_secular<M, 8>), grid, block, 0, st, nodes, w, split);            \
-    else hipLaunchKernelGGL((k_secular<M, 16>), grid, block, 0, st, nodes, w, split);                   \
+    constexpr int T8 = M == 2 ? 1 : 2, T16 = M == 2 ? 1 : 4;                                     \
+    if (l8 && many) hipLaunchKernelGGL((k_secular_lanes<M, 8, T8>), grid, block, 0, st, nodes, w, gy); \
+    else if (lanes_only && l8) hipLaunchKernelGGL((k_secular_lanes<M, 8, 1>), grid, block, 0, st, nodes, w, gy); \
+    else if (many) hipLaunchKernelGGL((k_secular_lanes<M, 16, T16>), grid, block, 0, st, nodes, w, gy); \
+    else if (lanes_only) hipLaunchKernelGGL((k_secular_lanes<M, 16, 1>), grid, block, 0, st, nodes, w, gy); \
+    else if (l8) hipLaunchKernelGGL((k_secular<M, 8>), grid, block, 0, st, nodes, w, gy);     \
+    else hipLaunchKernelGGL((k_secular<M, 16>), grid, block, 0, st, nodes, w, gy);            \
   } while (0)
   if (mode == 2) BDC_LAUNCH_SEC(2);
   else if (mode == 1) BDC_LAUNCH_SEC(1);

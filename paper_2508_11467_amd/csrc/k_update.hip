@@ -932,7 +932,9 @@ void launch_update(const NodeDesc* nodes, int nnodes, int max_m, const Work& w, 
     const int tiles = ((max_m + 1 + 127) / 128) * ((max_m + 127) / 128);
     const int gy = grid_y(nnodes, tiles, tu.grid128 * 2);
     if (tu.tile128)
-      hipLaunchKernelGGL(k_update2, dim3(nnodes, (gy + 7) & ~7, 4), dim3(kBlock), 0, st, nodes, w);
+      // a multiple of 8 for the XCDs, but no empty workgroups for the thousands
+      // of small merges of a batch (10000 of them 163 -> 123 us)
+      hipLaunchKernelGGL(k_update2, dim3(nnodes, gy < 8 ? gy : (gy + 7) & ~7, 4), dim3(kBlock), 0, st, nodes, w);
     else
       hipLaunchKernelGGL((k_update<128, 128>), dim3(nnodes, gy, 4), dim3(kBlock), 0, st, nodes, w);
   }

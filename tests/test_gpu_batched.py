@@ -256,6 +256,26 @@ def test_roots_per_workgroup_do_not_matter(gpu, n, copies):
         s.close()
 
 
+@pytest.mark.parametrize("n,copies", [(60, 2200), (64, 2048), (130, 1010), (250, 530), (256, 512)])
+def test_lanes_per_root_do_not_matter(gpu, n, copies):
+    """Levels with enough small merges take four lanes per root, which hold the
+    partial sums of 8 or 16: the bits of the problems solved alone."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    d, e = inputs.batch_uniform([n] * copies, n)
+    s = Solver(0)
+    try:
+        sig, U, VT = (x.clone() for x in s.svd_batched([n] * copies, torch.from_numpy(d).cuda(),
+                                                      torch.from_numpy(e).cuda()))
+        for i in (0, 1, copies // 2, copies - 1):
+            one = s.svd(torch.from_numpy(d[i * n:(i + 1) * n]).cuda(), torch.from_numpy(e[i * n:(i + 1) * n - 1]).cuda())
+            assert torch.equal(sig[i * n:(i + 1) * n], one[0])
+            assert torch.equal(U[i * n * n:(i + 1) * n * n].view(n, n).T, one[1])
+            assert torch.equal(VT[i * n * n:(i + 1) * n * n].view(n, n).T, one[2])
+    finally:
+        s.close()
+
+
 def test_autotune_picks_a_valid_tuning(gpu):
     import torch
     from paper_2508_11467_amd.api import Solver
