@@ -15,6 +15,7 @@
 #include <climits>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -85,11 +86,9 @@ struct bdc_handle_s {
   bool have_call = false;
   // captured launch sequence of the current plan (all of a call but its first
   // launch, which hands over the buffers)
-  hipStream_t cap_stream = nullptr;
-  // second stream of the captured sequence (each level's rotations and
-  // gather beside its secular solve, Löwner z and vectors) and its fork and
-  // join events
-  hipStream_t side_stream = nullptr;
+  bool captures = false;  // holds the device's capture stream
+  // fork and join of the captured sequence's second stream (each level's
+  // rotations and gather beside its secular solve, Löwner z and vectors)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipGraphExec_t gexec = nullptr;
   struct Rec {
@@ -531,6 +530,55 @@ int run_plan(bdc_handle_t h, hipStream_t st, hipStream_t side = nullptr) {
   return BDC_OK;
 }
 
+// The stream that solves are captured on: one per device, shared by the handles
+// that have captured (made by the first, destroyed with the last), one capture
+// at a time.  A stream holds one of the process's few hardware queues for as
+// long as it lives: with four taken before the first grid-wide launch
+// (bdc_geqrf, bdc_gebrd), whose queue is then the fifth, every kernel beside
+// that one ran about 16 us longer (QR of 20000 x 1000 after solves with two
+// handles, of two streams each, 16.5 ms; 10.4 this way).  A stream made for each
+// capture would cost a call with new sizes 60 us.
+struct DeviceCapture {
+  std::mutex capturing;
+  hipStream_t stream = nullptr;
+  int users = 0;
+};
+constexpr int kCaptureDevices = 64;
+DeviceCapture g_capture[kCaptureDevices];
+
+bool capture_stream_hold(int device) {
+  if (device >= kCaptureDevices) return false;
+  DeviceCapture& c = g_capture[device];
+  std::lock_guard<std::mutex> lock(c.capturing);
+  if (!c.stream && hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking) != hipSuccess) {
+    c.stream = nullptr;
+    return false;
+  }
+  ++c.users;
+  return true;
+}
+
+void capture_stream_drop(int device) {
+  DeviceCapture& c = g_capture[device];
+  std::lock_guard<std::mutex> lock(c.capturing);
+  if (--c.users == 0) {
+    (void)hipStreamDestroy(c.stream);
+    c.stream = nullptr;
+  }
+}
+
+// the capture stream for one capture, with a second stream beside it if asked
+struct CaptureLease {
+  std::lock_guard<std::mutex> lock;
+  hipStream_t main, side = nullptr;
+  CaptureLease(int device, bool two) : lock(g_capture[device].capturing), main(g_capture[device].stream) {
+    if (two && hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess) side = nullptr;
+  }
+  ~CaptureLease() {
+    if (side) (void)hipStreamDestroy(side);
+  }
+};
+
 int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, const double* e,
           double* sigma, double* U, double* VT, hipStream_t st) {
   DeviceGuard g(h->device);
@@ -569,16 +617,18 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
   // new ones: 130 us at n = 100, 0.5 ms at n = 16384)
   if (!h->gexec) {
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
-    if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
-      return BDC_ERR_HIP;
-    if (!h->side_stream && hipStreamCreateWithFlags(&h->side_stream, hipStreamNonBlocking) != hipSuccess)
-      return BDC_ERR_HIP;
+    if (!h->captures) {
+      if (!capture_stream_hold(h->device)) return BDC_ERR_HIP;
+      h->captures = true;
+    }
+    CaptureLease cap(h->device, h->tune.streams == 2);
+    if (h->tune.streams == 2 && !cap.side) return BDC_ERR_HIP;
     if (!h->ev_fork && hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
     if (!h->ev_join && hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
-    if (hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return BDC_ERR_HIP;
-    const int rc = run_plan(h, h->cap_stream, h->tune.streams == 2 ? h->side_stream : nullptr);
+    if (hipStreamBeginCapture(cap.main, hipStreamCaptureModeThreadLocal) != hipSuccess) return BDC_ERR_HIP;
+    const int rc = run_plan(h, cap.main, cap.side);
     hipGraph_t g = nullptr;
-    const hipError_t ec = hipStreamEndCapture(h->cap_stream, &g);
+    const hipError_t ec = hipStreamEndCapture(cap.main, &g);
     if (rc != BDC_OK || ec != hipSuccess || !g) {
       if (g) (void)hipGraphDestroy(g);
       return rc != BDC_OK ? rc : BDC_ERR_HIP;
@@ -665,8 +715,7 @@ int bdc_destroy(bdc_handle_t h) {
     DeviceGuard g(h->device);
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
     drop_graph(h);
-    if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
-    if (h->side_stream) (void)hipStreamDestroy(h->side_stream);
+    if (h->captures) capture_stream_drop(h->device);
     if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
     if (h->ev_join) (void)hipEventDestroy(h->ev_join);
     free_plan(h->plan);

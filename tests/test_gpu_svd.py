@@ -324,3 +324,41 @@ def test_new_buffers_between_calls(gpu, n, streams):
         for x, y in zip(out, want[i]):
             assert torch.equal(x, y)
     s.close()
+
+
+@pytest.mark.parametrize("streams", [1, 2])
+def test_handles_share_the_capture_stream(gpu, streams):
+    """Handles come and go in any order between captures: each solve's bits are
+    those of a handle by itself."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    want = {}
+    for n in (50, 300):
+        d, e = inputs.normal(n, n)
+        d, e = torch.from_numpy(d).cuda(), torch.from_numpy(e).cuda()
+        s = Solver(0)
+        want[n] = (d, e, [x.clone() for x in s.svd(d, e)])
+        s.close()
+
+    def check(s, n):
+        d, e, ref = want[n]
+        for x, y in zip(s.svd(d, e), ref):
+            assert torch.equal(x, y)
+
+    def handle():
+        s = Solver(0)
+        t = s.tuning()
+        s.set_tuning(**{k: t[k] for k in ("small_n", "flat", "grid64", "grid128", "sec_small_n")}, streams=streams)
+        return s
+    a, b = handle(), handle()
+    check(a, 50)
+    check(b, 300)
+    a.close()
+    check(b, 50)
+    c = handle()
+    b.close()
+    check(c, 300)
+    c.close()
+    c = handle()
+    check(c, 50)
+    c.close()
