@@ -478,7 +478,7 @@ def control_leg(steps: int, warmup: int) -> dict:
                 "moduli": L,
                 "int8_ops": L * st["split_flops"],
                 "frac_of_int8_mfma_peak": L * st["split_flops"] / t / PEAK_INT8_MFMA,
-                "note": "times the whole split stage (scaling, residues, int8 products, Garner rebuild)"}
+                "note": "times the whole split stage (scaling, residues, int8 products, rebuild)"}
         leg.update(sigma_errors(out[0], ref))
         leg.update(accuracy(d, e, out[0], out[1].T, out[2].T))
         res[form] = leg

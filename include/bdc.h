@@ -445,7 +445,7 @@ int bdc_step_gemm_ozaki(bdc_handle_t handle, int slices, int M, int N, int K, co
  * column of B is scaled by a power of two and rounded to an integer; the
  * integer product is formed exactly from its residues modulo `moduli`
  * (13..16) pairwise coprime odd moduli <= 255, each an int8 x int8 -> int32
- * product, and rebuilt by Garner's mixed-radix algorithm.  The scale is the
+ * product, and rebuilt by the theorem's sum.  The scale is the
  * largest one for which the rebuilt product is exact (K <= 2^20), so the
  * error comes only from rounding A and B at about 2^-beta of each row's /
  * column's largest entry, beta = min(55, floor((log2 prod m - 1 - log2 K) / 2))
