@@ -558,14 +558,15 @@ __device__ void secular_wide(const NodeDesc& nd, int N, const Work& w, int ny, W
 }
 
 // Secular roots of a node with at most kLanesMaxN kept values, L lanes per
-// root (L = 8 or 16; 256/L roots per 256-thread workgroup).  Lane `part` of a
-// root sums the poles j = part (mod L) in ascending order into left (j <= lp)
-// and right sums, so every lane of a wavefront makes the same number of steps
-// whatever its root's interval (the summation order inside a lane differs
-// from the wide kernel's far-to-near order on the right side); the L partial sums are combined with DPP row
+// root (L = 8 or 16; 256/L roots per 256-thread workgroup), or L/T with T of
+// the L sums each.  Sum `part` of a root takes the poles j = part (mod L) in
+// ascending order into left (j <= lp) and right sums, so every lane of a
+// wavefront makes the same number of steps whatever its root's interval (the
+// summation order inside a lane differs from the wide kernel's far-to-near
+// order on the right side); the L partial sums are combined with DPP row
 // permutations (no LDS, no barrier), and every lane of a root advances the
-// same iteration state.  A wavefront holds 64/L roots, so it iterates only as
-// long as the slowest of those few.
+// same iteration state.  A wavefront holds 64/L (64 T/L) roots, so it iterates
+// only as long as the slowest of those few.
 constexpr int kLanesMaxN = kSecLanesMaxN;
 constexpr int64_t kSecMany = 131072;  // positions of a level from which four lanes take a root
 // The lanes-per-root kernel's network: at most 32 rows (its roots per
@@ -684,8 +685,8 @@ __device__ void secular_lanes(const NodeDesc& nd, int N, const Work& w, LanesLds
 // rotations of its deflated pairs and the gather of its kept columns.  They
 // and the secular solve need the deflation's lists only, and none reads what
 // another writes, so one launch holds all three: two launches less per level
-// (about 4.5 us each: n = 1000, five levels, 488 -> 443 us; n = 16384 1934 ->
-// 1722), and the columns, bound by memory, move while the roots, bound by
+// (4.4 and 6.6 us by themselves at n = 1000, five levels: 488 -> 443 us; n =
+// 16384 1934 -> 1722), and the columns, bound by memory, move while the roots, bound by
 // arithmetic, are found (the 2000-problem batch 21.7 -> 20.6 ms, n = 6000 with
 // nothing deflated 11.0 -> 10.6).
 __device__ inline bool columns_part(const NodeDesc& nd, const Work& w, int ny) {
