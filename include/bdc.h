@@ -262,8 +262,8 @@ int bdc_step_gemm(bdc_handle_t handle, int M, int N, int K, const double* A, int
  * reflectors y_rs = 1, y_cs = ld; row-stored ones y_rs = ld, y_cs = 1, with
  * offset 1 for gebrd's row reflectors); tau[i] = 0 makes H_i the identity.
  * All pointers are device pointers; Y and tau are not written.  The
- * reflectors are applied `block` at a time (1..64; 0 = 64, of which up to
- * eight blocks go together, or one where a workspace cap holds no more) in
+ * reflectors are applied `block` at a time (1..64; 0 = 64, of which
+ * two blocks go together, or one where a workspace cap holds no more) in
  * the modified compact WY form of eq. inv_t / larft_update: T^{-1} = Y^T Y above its
  * diagonal and 1/tau_i on it (gemm), Z = Y^T C (gemm), Z = T^{-1} \ Z (trsm),
  * C = C - Y Z (gemm), on the FP64 matrix cores.  Scratch is owned by the

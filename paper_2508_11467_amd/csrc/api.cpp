@@ -1025,9 +1025,7 @@ int bdc_orgqr(bdc_handle_t h, int m, int ncols, int k, const double* A, int lda,
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  // half the largest group: Q's leading columns, zero below their own group's
-  // pivots, are multiplied in full by every group before theirs
-  const int rc = ensure_bt(h, m, ncols, block, backtr_group(block, kBtMaxGroup / 2), &plan);
+  const int rc = ensure_bt(h, m, ncols, block, backtr_group(block, kBtMaxGroup), &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_orgqr(m, ncols, k, A, lda, tau, Q, ldq, plan, h->bt_arena, st);

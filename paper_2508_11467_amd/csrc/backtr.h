@@ -9,7 +9,7 @@
 namespace bdc {
 
 constexpr int kBtMaxBlock = 64;  // reflectors per block, at most
-constexpr int kBtMaxGroup = 512; // reflectors applied together, at most (eight blocks of 64)
+constexpr int kBtMaxGroup = 128; // reflectors applied together, at most (two blocks of 64)
 
 // the allocation-free entry point: a fixed 32 MiB of device memory per GPU,
 // C taken in panels of at most 512 columns

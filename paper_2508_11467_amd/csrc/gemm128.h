@@ -56,14 +56,20 @@ __device__ inline void gemm128_place(int v, int P, int tiles_m, int tiles_n, int
 // with TRANSA.  store(row, col, value) for the tile's elements inside M x N, or,
 // with Store::kReads, store(row, col, store.at(row, col), value).
 // Sums run over k ascending in steps of four from k0.  256 threads.  TM = 64
-// or 32 (a transposed A only) is for products of so few rows.
-template <bool TRANSA, int TM = 128, class Store>
+// or 32 (a transposed A only) is for products of so few rows, and for sums over
+// a long depth: they run in chains of CHAIN slabs (a power of two; 0: one
+// chain), each from zero, which are added up one by one, so that a term passes
+// through a chain's roundings and not through the whole depth's.  (A chain's
+// sums and the total take two sets of accumulators, for which 128 rows have no
+// registers with two workgroups per CU.)
+template <bool TRANSA, int TM = 128, int CHAIN = 0, class Store>
 __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A, int64_t lda,
                                     const double* __restrict__ B, int64_t ldb, int M, int N, int k0, int k1, int tm0,
                                     int tn0, const Store& store) {
   constexpr int TK = kG128K;
   constexpr int BA = TM / 32;  // 16 x 16 blocks of a wavefront's rows; lines of a transposed A per thread
   static_assert(TM == 128 || ((TM == 64 || TM == 32) && TRANSA), "tile");
+  static_assert(CHAIN == 0 || (TM < 128 && (CHAIN & (CHAIN - 1)) == 0), "chain");
   const int t = threadIdx.x, wv = t >> 6, l = t & 63;
   const int wm = wv & 1, wn = wv >> 1;
   const int li = l & 15, lk = l >> 4;
@@ -147,6 +153,30 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
           acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(bf[b], af[a], acc[a][b], 0, 0, 0);
     }
   };
+  g128_acc total[CHAIN ? BA : 1][4];
+  int slabs = 0;  // of the chain
+  auto chain_end = [&] {
+    if constexpr (CHAIN > 0) {
+#pragma unroll
+      for (int a = 0; a < BA; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          total[a][b] += acc[a][b];
+          acc[a][b] = g128_acc{0.0, 0.0, 0.0, 0.0};
+        }
+    }
+  };
+  auto step = [&](int buf) {
+    multiply(buf);
+    if constexpr (CHAIN > 0)
+      if ((++slabs & (CHAIN - 1)) == 0) chain_end();
+  };
+  if constexpr (CHAIN > 0) {
+#pragma unroll
+    for (int a = 0; a < BA; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) total[a][b] = g128_acc{0.0, 0.0, 0.0, 0.0};
+  }
   int kb = k0, buf = 0;
   __syncthreads();  // the previous tile's readers are done with both buffers
   const int nfull = narrow ? (k1 - k0) / TK : 0;
@@ -156,12 +186,12 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
     __syncthreads();
     for (int sl = 1; sl < nfull; ++sl) {
       load(k0 + sl * TK);
-      multiply(buf);
+      step(buf);
       buf ^= 1;
       stash(buf, last_row);
       __syncthreads();
     }
-    multiply(buf);
+    step(buf);
     buf ^= 1;
     kb += nfull * TK;
   }
@@ -169,9 +199,10 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
     load_tested(kb);
     stash(buf, false);
     __syncthreads();
-    multiply(buf);
+    step(buf);
     buf ^= 1;
   }
+  chain_end();
   // The products are taken as B^T A^T: D[i][j] of a 16x16 block sits in lane
   // j + 16 * (i % 4), register i / 4, so with i the column and j the row a
   // wavefront's access is 16 consecutive rows of four columns (whole 128-byte
@@ -196,8 +227,11 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
       for (int r = 0; r < 4; ++r) {
         const int col = col0 + b * 16 + 4 * r;
         if (row >= M || col >= N) continue;
-        if constexpr (Store::kReads) store(row, col, old[b][r], acc[a][b][r]);
-        else store(row, col, acc[a][b][r]);
+        double v;
+        if constexpr (CHAIN > 0) v = total[a][b][r];
+        else v = acc[a][b][r];
+        if constexpr (Store::kReads) store(row, col, old[b][r], v);
+        else store(row, col, v);
       }
   }
 }

@@ -14,14 +14,20 @@
 // whose partial sums are added in a fixed order (deterministic).
 //
 // The group.  C crosses HBM three times per group (read for W, read and
-// written for the update), 24 bytes per entry against 4 K flops: at K = 64
-// that is the bound (and the update's epilogue with it), from K = 512 on the
-// matrix cores are.  Eight 64-blocks therefore go as one group, the
-// triangular solve by 64-row blocks with inverted diagonal blocks, on the
-// matrix cores too.  8192 x 8192 with 8192 reflectors: 22.3 ms (49 TFLOP/s)
-// with groups of 512, 26 with 256, and 69.9 with 64 and one thread per
-// column in the solve (113 us a block, whatever its size); 3001 x 3001: 2.3,
-// 2.9 and 11.3 ms.
+// written for the update), 24 bytes per entry against 4 K flops, so K = 64 is
+// bound by it and wider groups by the matrix cores; but the error grows with
+// the group, as the reflectors of a group see each other through the rounded
+// Y^T Y alone.  Against extended precision (rms, relative to blocks of 64 with
+// sums over 256 to 512 rows and one back substitution per column): groups of 512
+// with sums over up to 4096 rows 1.2 to 2 times for random reflectors, 2 to 4
+// times for nearly parallel ones; groups of 128 with the sums of Y^T [C | Y] in
+// chains of 64 rows 0.5 to 0.9 for both (200 to 40000 rows; groups of 256 up to
+// 1.25 for parallel ones).  So two 64-blocks go as one group, the triangular
+// solve by 64-row blocks with inverted diagonal blocks, on the matrix cores too.
+// 8192 x 8192 with 8192 reflectors: 30.0 ms with groups of 128 (the update 14.5,
+// Y^T [C | Y] 13.4), 22.0 with 512, and 69.9 with 64 and one thread per column in
+// the solve (113 us a block, whatever its size); 3001 x 3001: 2.96, 2.23 and
+// 11.2 ms.
 #include <algorithm>
 #include <mutex>
 
@@ -36,6 +42,7 @@ namespace {
 constexpr int kTB = 64;        // block of the triangular solve
 constexpr int kSolveCols = 16; // columns of W per workgroup of the solve
 constexpr int kTSlice = 512;   // depth slice of Y^T Y
+constexpr int kChain = 64;     // rows that the sums of Y^T [C | Y] run over at a time
 
 struct PartStore {
   static constexpr bool kReads = false;
@@ -99,7 +106,7 @@ __global__ __launch_bounds__(256) void k_bt_pack(const double* __restrict__ Y, i
 // are C's (slices of `slice` rows), the last ones Y's own (kTSlice
 // rows; the tiles on or above the diagonal).  Tile columns 8 apart, so that
 // the row tiles of one tile column (which read the same part of C) fall on one
-// XCD.
+// XCD.  Each sum runs in chains of kChain rows.
 template <int TM>
 __global__ __launch_bounds__(256, 2) void k_bt_ytx(const double* __restrict__ Yp, const double* __restrict__ C,
                                                    int64_t ldc, int rows, int bw, int N, int slice,
@@ -119,8 +126,9 @@ __global__ __launch_bounds__(256, 2) void k_bt_ytx(const double* __restrict__ Yp
     if (c >= tc) return;
   }
   const int len = own ? kTSlice : slice, k0 = z * len, k1 = min(rows, k0 + len);
-  gemm128_tile<true, TM>(sm, Yp, rows, own ? Yp : C, own ? (int64_t)rows : ldc, bw, own ? bw : N, k0, k1, r * TM,
-                         c * 128, PartStore{own ? PT + (int64_t)z * bw * bw : P + (int64_t)z * bw * N, bw});
+  gemm128_tile<true, TM, kChain / kG128K>(sm, Yp, rows, own ? Yp : C, own ? (int64_t)rows : ldc, bw, own ? bw : N, k0,
+                                          k1, r * TM, c * 128,
+                                          PartStore{own ? PT + (int64_t)z * bw * bw : P + (int64_t)z * bw * N, bw});
 }
 
 // out += the slices in order (out starts at zero with first)
@@ -211,7 +219,7 @@ __global__ __launch_bounds__(1024) void k_bt_tinv(const double* __restrict__ PT,
 // Z = T^{-1} \ W (upper, from the last 64-row block up) or T^{-T} \ W (lower,
 // from the first block down); W is the sum of prev (if any) and the slices, in
 // order.  A chain of block rows, so it is bound by latency: a block's
-// operands are read together, 35 us for 256 x 8192 (70 with
+// operands are read together, 17 us for 128 x 8192 (256 x 8192: 35, and 70 with
 // eight loads in flight), and 16 columns to a workgroup keep the chip's CUs
 // in it.  kSolveCols columns per workgroup in LDS; for each block row the
 // products with the blocks solved before it, then with the inverted diagonal
@@ -324,14 +332,18 @@ constexpr int kBtChunkSlices = 16;
 constexpr size_t kBtChunkDoubles = size_t(1) << 19;
 constexpr int kBtChunkT = 2 * kTSlice;
 
+// rows of a tile of Y^T [C | Y] for K reflectors
+constexpr int bt_tile_rows(int K) { return K <= 32 ? 32 : 64; }
+
 // Depth slice of W = Y^T C for `rows` rows, p columns and groups of K: the
 // multiple of 128 (up to 4096 rows) that costs least by a plain count of the
-// tiles per CU (two at a time on 256 CUs, 256 cycles per 128 x 128 tile and
-// row of depth; Y^T Y's share beside them) and the partial sums' traffic
+// tiles per CU (two at a time on 256 CUs, 2 cycles per row of a 128-column tile
+// and row of depth; Y^T Y's share beside them) and the partial sums' traffic
 // (written and read, 2000 bytes a cycle).  A function of rows, p and K only,
 // so every panel width and chunk adds in the same order.
 int bt_slice(int rows, int p, int K) {
-  const int64_t tr = (K + 127) / 128, tiles = tr * ((p + 127) / 128);
+  const int tm = bt_tile_rows(K);
+  const int64_t tr = (K + tm - 1) / tm, tiles = tr * ((p + 127) / 128), own = tr * ((K + 127) / 128);
   int best = kBtSliceRows;
   double cost = 1e300;
   for (int n = (rows + kBtSliceRows - 1) / kBtSliceRows; n <= kBtSlices; ++n) {
@@ -339,9 +351,9 @@ int bt_slice(int rows, int p, int K) {
     if (s > kBtSliceRows) continue;
     const int64_t z = (rows + s - 1) / s;
     if (cost < 1e300 && (size_t)z * K * p > kBtSliceDoubles) break;
-    const int64_t wg = tiles * z + (tr * (tr + 1) / 2 * rows + s - 1) / s, rest = wg % 512;
+    const int64_t wg = tiles * z + (own * rows + s - 1) / s, rest = wg % 512;
     const double units = 2.0 * (wg / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : 2.0);
-    const double c = units * std::min(s, rows) * 256.0 + (double)z * K * p * 16.0 / 2000.0;
+    const double c = units * std::min(s, rows) * 2.0 * tm + (double)z * K * p * 16.0 / 2000.0;
     if (c < cost) {
       cost = c;
       best = s;
@@ -407,7 +419,7 @@ void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, 
     // rows of a chunk: whole slices of W
     const int chunk = plan.fixed ? slice * std::min(kBtChunk / slice, plan.slices) : rows;
     const int nchunk = (rows + chunk - 1) / chunk;
-    const int tm = bw <= 32 ? 32 : bw <= 64 ? 64 : 128, tr = (bw + tm - 1) / tm, tt = (bw + 127) / 128;
+    const int tm = bt_tile_rows(bw), tr = (bw + tm - 1) / tm, tt = (bw + 127) / 128;
     auto pack = [&](int q0, int q1) {
       const int64_t tot = (int64_t)(q1 - q0) * bw;
       hipLaunchKernelGGL(k_bt_pack, dim3((unsigned)std::min<int64_t>((tot + 255) / 256, 4096)), dim3(256), 0, st, Y,
@@ -417,12 +429,8 @@ void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, 
     auto ytx = [&](const double* X, int pw, int cr, int nz, int nzt) {
       const int cblocks = ((pw + 127) / 128 + 7) / 8 * 8 * tr * nz;
       const dim3 grid(cblocks + tr * tt * nzt);
-      if (tm == 32)
-        hipLaunchKernelGGL(k_bt_ytx<32>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);
-      else if (tm == 64)
-        hipLaunchKernelGGL(k_bt_ytx<64>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);
-      else
-        hipLaunchKernelGGL(k_bt_ytx<128>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw, pw, slice, P, cblocks, PT);
+      hipLaunchKernelGGL(tm == 32 ? k_bt_ytx<32> : k_bt_ytx<64>, grid, dim3(256), 0, st, Yp, X, (int64_t)ldc, cr, bw,
+                         pw, slice, P, cblocks, PT);
     };
     auto accumulate = [&](const double* part, int64_t n, int slices, bool first, double* sum) {
       hipLaunchKernelGGL(k_bt_accumulate, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, n, slices, first,
