@@ -233,3 +233,35 @@ def test_geqrf_is_bitwise_reproducible(solver):
     F1, t1, Q1 = _gpu_qr(solver, A)
     F2, t2, Q2 = _gpu_qr(solver, A)
     assert np.array_equal(F1, F2) and np.array_equal(t1, t2) and np.array_equal(Q1, Q2)
+
+
+def _factorisation_error(A, F, tau):
+    """Largest columnwise ||A - H_0 H_1 ... [R; 0]|| / ||A|| and the departure
+    of tau from 2 / y^T y, in extended precision."""
+    m, n = A.shape
+    Y = np.tril(F, -1).astype(np.longdouble)
+    Y[np.arange(n), np.arange(n)] = 1
+    E = np.zeros((m, n), np.longdouble)
+    E[:n] = np.triu(F[:n])
+    for i in range(n - 1, -1, -1):
+        E[i:] -= np.outer(np.longdouble(tau[i]) * Y[i:, i], Y[i:, i] @ E[i:])
+    fac = np.max(np.linalg.norm((A - E).astype(np.float64), axis=0) / np.linalg.norm(A, axis=0))
+    dev = np.max(np.abs(tau * np.sum(Y * Y, axis=0) / 2 - 1))
+    return float(fac), float(dev)
+
+
+@pytest.mark.parametrize("m,n", [(700, 200), (500, 96)])
+def test_geqrf_with_cancelling_columns(solver, m, n):
+    """Chebyshev polynomials on equidistant points, whose columns lose most of
+    themselves to the earlier ones: R, the reflectors and tau are as accurate as
+    the oracle's column-by-column factorisation, up to the bit that a column's
+    sum of squares may lose within a step (a factor of two)."""
+    x = np.linspace(-1.0, 1.0, m)[:, None]
+    A = np.cos(np.arange(n) * np.arccos(x))
+    F, tau, _ = _gpu_qr(solver, A)
+    R0, Y0, tau0 = hh.qr(A)
+    F0 = np.tril(Y0, -1)
+    F0[:n] += np.triu(R0)
+    got, ref = _factorisation_error(A, F, tau), _factorisation_error(A, F0, tau0)
+    print(f"{m}x{n}: factorisation {got[0]:.2e} (oracle {ref[0]:.2e}), tau {got[1]:.2e} ({ref[1]:.2e})", flush=True)
+    assert got[0] <= 2 * ref[0] and got[1] <= 2 * ref[1]
