@@ -30,6 +30,7 @@ SOURCES = {
     "k_qr.hip": [],
     "k_gebrd.hip": [],
     "plan.cpp": [],
+    "backtr_plan.cpp": [],
     "api.cpp": [],
     "api_steps.cpp": [],
 }

@@ -917,6 +917,9 @@ int grow_bt(bdc_handle_t h, size_t bytes) {
   if (h->opt.workspace_cap_bytes && h->arena_bytes + bytes > h->opt.workspace_cap_bytes) return BDC_ERR_NOMEM;
   if (hipMalloc(&h->bt_arena, bytes) != hipSuccess) {
     h->bt_arena = nullptr;
+    // the runtime keeps the error until it is read: not for the launches of a
+    // call that goes on with less
+    (void)hipGetLastError();
     return BDC_ERR_NOMEM;
   }
   h->bt_bytes = bytes;

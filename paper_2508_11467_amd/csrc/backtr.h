@@ -18,6 +18,12 @@ constexpr int kBtFixedPanel = 512;
 constexpr int kBtFixedWidth = 256;  // columns at a time within the fixed scratch
 constexpr int kBtMaxDevices = 64;
 
+constexpr int kTB = 64;                // block of the triangular solve
+constexpr int kTSlice = 512;           // depth slice of Y^T Y
+constexpr int kBtSliceRows = 4096;     // rows of a slice of W, at most
+constexpr int kBtChunk = kBtSliceRows; // the fixed scratch: rows of a chunk
+constexpr int kBtChunkT = 2 * kTSlice; // and of a chunk of Y^T Y
+
 // Scratch of one back-transformation: offsets in doubles, all bytes.
 struct BtPlan {
   int group, panel;  // reflectors applied together; columns of C at a time
@@ -32,6 +38,10 @@ size_t backtr_limit_bytes(int m, int panel, int block);
 // reflectors applied together for a block size
 inline int backtr_group(int block, int most) { return block == kBtMaxBlock ? most : block; }
 BtPlan backtr_plan(int m, int p, int panel, int group, bool fixed);
+// rows of a tile of Y^T [C | Y] for K reflectors
+constexpr int bt_tile_rows(int K) { return K <= 32 ? 32 : 64; }
+// depth slice of W for `rows` rows, p columns and groups of K
+int bt_slice(int rows, int p, int K);
 
 // C (m x p, ldc) <- Q C (trans 0) or Q^T C (trans 1), Q = H_0 ... H_{k-1};
 // reflector i has its unit pivot at row i + offset, zeros above, and entry r

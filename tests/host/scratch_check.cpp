@@ -1,0 +1,194 @@
+// Host check of what the C entry points do with their scratch
+// (paper_2508_11467_amd/csrc/api.cpp), built without a GPU by
+// tests/test_host_scratch.py: the HIP runtime is a small fake (memory with a
+// limit, a last error that stays until it is read, counters), the launchers
+// note the plans that they are given.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+
+#include "backtr.h"
+#include "bdc.h"
+#include "bdc_internal.h"
+#include "gebrd.h"
+#include "qr.h"
+
+using namespace bdc;
+
+static int fails = 0;
+#define CHECK(c)                                                          \
+  do {                                                                    \
+    if (!(c)) {                                                           \
+      std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); \
+      ++fails;                                                            \
+    }                                                                     \
+  } while (0)
+
+// ---------------------------------------------------------------- the fake runtime
+static size_t g_limit = SIZE_MAX, g_used = 0;  // device memory
+static std::map<void*, size_t> g_mem;
+static hipError_t g_last = hipSuccess;
+static int g_mallocs = 0, g_frees = 0, g_syncs = 0;
+static int g_devices = 1;
+
+static int traffic() { return g_mallocs + g_frees + g_syncs; }
+
+static hipError_t fail(hipError_t e) { return g_last = e; }
+
+extern "C" {
+hipError_t hipGetDeviceCount(int* n) { return *n = g_devices, hipSuccess; }
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes) {
+  ++g_mallocs;
+  if (bytes > g_limit - g_used) return *p = nullptr, fail(hipErrorOutOfMemory);
+  *p = std::malloc(1);
+  g_mem[*p] = bytes;
+  g_used += bytes;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  ++g_frees;
+  g_used -= g_mem.at(p);
+  g_mem.erase(p);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) {
+  const hipError_t e = g_last;
+  g_last = hipSuccess;
+  return e;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return ++g_syncs, hipSuccess; }
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemset(void*, int, size_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)1, hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEvent_t)1, hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 0.0f, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)2, hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { return *g = (hipGraph_t)3, hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  return *e = (hipGraphExec_t)4, hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+}
+
+// ---------------------------------------------------------------- the launchers
+static BtPlan g_plan{};       // of the last back-transformation
+static size_t g_scratch = 0;  // and the bytes of its scratch
+
+static void note(const BtPlan& plan, void* scratch) {
+  g_plan = plan;
+  g_scratch = g_mem.at(scratch);
+  CHECK(plan.bytes <= g_scratch);
+}
+
+namespace bdc {
+void launch_backtr(int, int, int, int, int, const double*, int64_t, int64_t, const double*, double*, int,
+                   const BtPlan& plan, void* scratch, hipStream_t) {
+  note(plan, scratch);
+}
+int launch_geqrf(int, int, int, double*, int, double*, int, void*, size_t, const BtPlan& plan, void* scratch,
+                 hipStream_t) {
+  note(plan, scratch);
+  return BDC_OK;
+}
+void launch_orgqr(int, int, int, const double*, int, const double*, double*, int, const BtPlan& plan, void* scratch,
+                  hipStream_t) {
+  note(plan, scratch);
+}
+void* backtr_fixed_scratch(int) { return nullptr; }
+size_t qr_sync_bytes(int) { return 4096; }
+int qr_max_block() { return 64; }
+int gebrd_max_block() { return 32; }
+size_t gebrd_work_bytes(int m, int n, int b, int) { return 16 * (size_t)b * (m + n); }
+int launch_gebrd(int, int, int, double*, int, double*, double*, double*, double*, int, void*, size_t, int,
+                 hipStream_t) {
+  return BDC_OK;
+}
+int oz_supported(int) { return 1; }
+bool crt_supported(int) { return true; }
+int mlp_parts(int) { return 1; }
+size_t mlp_pack_bytes() { return 8; }
+void launch_reset(Ctl*, NodeState*, SecCount*, int, const Io&, hipStream_t) {}
+void launch_leaf(const LeafDesc*, int, int, const Work&, hipStream_t) {}
+void launch_prep(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_rotate(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_gather(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_secular(const NodeDesc*, int, int, bool, const Work&, hipStream_t) {}
+void launch_lowner(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_vectors(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_order(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_update(const NodeDesc*, int, int, const Work&, const Tuning&, hipStream_t) {}
+void launch_update_crt(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_update_ozaki(const NodeDesc*, int, int, const Work&, hipStream_t) {}
+void launch_harvest(const NodeDesc*, int, int, const Work&, const Harvest&, hipStream_t) {}
+void launch_final_single(int64_t, const Work&, hipStream_t) {}
+void launch_final(const int64_t*, const int64_t*, const int64_t*, const int64_t*, const int64_t*, const int32_t*,
+                  const int32_t*, int64_t, int64_t, const Work&, hipStream_t) {}
+void launch_mlp_pack(const float*, unsigned short*, hipStream_t) {}
+void launch_mlp_forward(const float*, const float*, int, float*, hipStream_t) {}
+void launch_mlp_grad(const float*, const float*, const float*, const int*, int, float*, float*, hipStream_t) {}
+void launch_adam(float*, float*, float*, const float*, int, const float*, float*, float*, int, float, float,
+                 hipStream_t) {}
+}  // namespace bdc
+
+// ---------------------------------------------------------------- the checks
+static double d_arg;  // stands for any device array
+
+static bdc_handle_t handle(size_t cap = 0, int device = 0) {
+  bdc_options_t o;
+  bdc_default_options(&o);
+  o.workspace_cap_bytes = cap;
+  bdc_handle_t h = nullptr;
+  CHECK(bdc_create(&h, device, &o) == BDC_OK);
+  return h;
+}
+
+static int apply(bdc_handle_t h, int m, int p, int k, int block = 0) {
+  return bdc_apply_reflectors(h, 0, m, p, k, 0, &d_arg, 1, m, &d_arg, &d_arg, m, block, nullptr);
+}
+static int geqrf(bdc_handle_t h, int m, int n) { return bdc_geqrf(h, m, n, &d_arg, m, &d_arg, 0, nullptr); }
+static int orgqr(bdc_handle_t h, int m, int n) {
+  return bdc_orgqr(h, m, n, n, &d_arg, m, &d_arg, &d_arg, m, 0, nullptr);
+}
+
+// Memory that holds the scratch of one block at a time but not that of a
+// group: the call is served and reports no error, and neither does the next.
+static void out_of_memory() {
+  const int m = 3000, p = 700, k = 900;
+  bdc_handle_t h = handle();
+  g_limit = backtr_limit_bytes(m, p, 64);
+  CHECK(backtr_plan(m, p, p, kBtMaxGroup, false).bytes > g_limit);
+  CHECK(apply(h, m, p, k) == BDC_OK);
+  CHECK(g_plan.group == 64 && g_plan.fixed);
+  CHECK(apply(h, m, p, k) == BDC_OK);
+  CHECK(orgqr(h, m, p) == BDC_OK);
+  // and where there is none at all, the status says so
+  g_limit = g_used;
+  CHECK(apply(h, 2 * m, p, k) == BDC_ERR_NOMEM);
+  g_limit = SIZE_MAX;
+  CHECK(apply(h, m, p, k) == BDC_OK);
+  CHECK(bdc_destroy(h) == BDC_OK);
+}
+
+int main(int argc, char** argv) {
+  const std::string which = argc > 1 ? argv[1] : "";
+  if (which == "out_of_memory") out_of_memory();
+  else return 2;
+  CHECK(g_mem.empty());
+  std::printf("%s: %d failures\n", which.c_str(), fails);
+  return fails != 0;
+}
