@@ -104,6 +104,7 @@ struct bdc_handle_s {
   size_t oz_bytes = 0;
   void* bt_arena = nullptr;   // back-transformation scratch (grown on demand)
   size_t bt_bytes = 0;
+  size_t bt_refused = SIZE_MAX;  // the least that was asked of it and not to be had
   void* bt_fixed = nullptr;   // this device's fixed scratch (allocation-free back-transformation)
   void* qr_sync = nullptr;    // QR panel: places of its sums over the grid
   size_t qr_sync_size = 0;
@@ -907,14 +908,18 @@ int reflector_args(bdc_handle_t h, int trans, int m, int p, int k, int offset, c
 }  // namespace
 
 namespace {
+bool cap_admits(bdc_handle_t h, size_t bytes) {
+  return !h->opt.workspace_cap_bytes || h->arena_bytes + bytes <= h->opt.workspace_cap_bytes;
+}
+
 // the handle's back-transformation scratch, grown to at least `bytes`
 int grow_bt(bdc_handle_t h, size_t bytes) {
   if (h->bt_bytes >= bytes) return BDC_OK;
+  if (!cap_admits(h, bytes)) return BDC_ERR_NOMEM;
   if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
   if (h->bt_arena) (void)hipFree(h->bt_arena);
   h->bt_arena = nullptr;
   h->bt_bytes = 0;
-  if (h->opt.workspace_cap_bytes && h->arena_bytes + bytes > h->opt.workspace_cap_bytes) return BDC_ERR_NOMEM;
   if (hipMalloc(&h->bt_arena, bytes) != hipSuccess) {
     h->bt_arena = nullptr;
     // the runtime keeps the error until it is read: not for the launches of a
@@ -927,12 +932,19 @@ int grow_bt(bdc_handle_t h, size_t bytes) {
 }
 
 // scratch and plan for m rows and p columns; where the memory for large
-// groups is not to be had, one group per block with the rows in chunks
+// groups is not to be had, one group per block with the rows in chunks.  What
+// memory has once refused is not tried again, so that a call that is served
+// with less neither waits nor allocates the next time.
 int ensure_bt(bdc_handle_t h, int m, int p, int block, int group, BtPlan* plan) {
   *plan = backtr_plan(m, p, p, group, false);
-  if (grow_bt(h, plan->bytes) == BDC_OK) return BDC_OK;
+  const size_t had = h->bt_bytes;
+  if (had >= plan->bytes) return BDC_OK;
+  if (plan->bytes < h->bt_refused && cap_admits(h, plan->bytes)) {
+    if (grow_bt(h, plan->bytes) == BDC_OK) return BDC_OK;
+    h->bt_refused = plan->bytes;
+  }
   *plan = backtr_plan(m, p, p, block, true);
-  return grow_bt(h, plan->bytes);
+  return grow_bt(h, std::max(plan->bytes, had));
 }
 }  // namespace
 

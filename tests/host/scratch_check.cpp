@@ -184,9 +184,34 @@ static void out_of_memory() {
   CHECK(bdc_destroy(h) == BDC_OK);
 }
 
+// Where a cap, or the memory there is, admits only one block at a time, the
+// scratch is kept from call to call like any other: the second round of calls
+// allocates, frees and waits for nothing.
+static void kept() {
+  const int m = 3000, p = 700, k = 900;
+  for (int capped = 0; capped < 2; ++capped) {
+    const size_t most = backtr_limit_bytes(m, p, 64);
+    bdc_handle_t h = handle(capped ? most : 0);
+    g_limit = capped ? SIZE_MAX : most + qr_sync_bytes(1);
+    for (int round = 0; round < 3; ++round) {
+      const int before = traffic();
+      CHECK(apply(h, m, p, k) == BDC_OK && g_plan.group == 64 && g_plan.fixed);
+      CHECK(orgqr(h, m, p) == BDC_OK && g_plan.group == 64);
+      CHECK(geqrf(h, m, p) == BDC_OK);
+      CHECK(apply(h, m - 100, p, k) == BDC_OK);
+      if (round > 0) CHECK(traffic() == before);
+    }
+    // a scratch that fits is still had
+    CHECK(apply(h, 500, 100, 300) == BDC_OK && g_plan.group == kBtMaxGroup);
+    g_limit = SIZE_MAX;
+    CHECK(bdc_destroy(h) == BDC_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
+  else if (which == "kept") kept();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);
