@@ -931,20 +931,32 @@ int grow_bt(bdc_handle_t h, size_t bytes) {
   return BDC_OK;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) == hipSuccess) return c == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 // scratch and plan for m rows and p columns; where the memory for large
-// groups is not to be had, one group per block with the rows in chunks.  What
-// memory has once refused is not tried again, so that a call that is served
-// with less neither waits nor allocates the next time.
-int ensure_bt(bdc_handle_t h, int m, int p, int block, int group, BtPlan* plan) {
+// groups is not to be had, one group per block with the rows in chunks (whose
+// scratch any earlier call of these sizes has left, so that a captured call
+// need not allocate, however many reflectors it has).  What memory has once
+// refused is not tried again, so that a call that is served with less neither
+// waits nor allocates the next time.
+int ensure_bt(bdc_handle_t h, int m, int p, int block, int group, hipStream_t st, BtPlan* plan) {
   *plan = backtr_plan(m, p, p, group, false);
   const size_t had = h->bt_bytes;
   if (had >= plan->bytes) return BDC_OK;
-  if (plan->bytes < h->bt_refused && cap_admits(h, plan->bytes)) {
-    if (grow_bt(h, plan->bytes) == BDC_OK) return BDC_OK;
-    h->bt_refused = plan->bytes;
+  const BtPlan least = backtr_plan(m, p, p, block, true);
+  const size_t both = std::max(plan->bytes, least.bytes);
+  const size_t want = cap_admits(h, both) ? both : plan->bytes;
+  if (want < h->bt_refused && cap_admits(h, want) && !(had >= least.bytes && capturing(st))) {
+    if (grow_bt(h, want) == BDC_OK) return BDC_OK;
+    h->bt_refused = want;
   }
-  *plan = backtr_plan(m, p, p, block, true);
-  return grow_bt(h, std::max(plan->bytes, had));
+  *plan = least;
+  return grow_bt(h, std::max(least.bytes, had));
 }
 }  // namespace
 
@@ -955,7 +967,7 @@ int bdc_apply_reflectors(bdc_handle_t h, int trans, int m, int p, int k, int off
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  const int rc = ensure_bt(h, m, p, block, backtr_group(block, kBtMaxGroup), &plan);
+  const int rc = ensure_bt(h, m, p, block, backtr_group(block, k), (hipStream_t)stream, &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_backtr(trans, m, p, k, offset, Y, y_rs, y_cs, tau, C, ldc, plan, h->bt_arena, st);
@@ -972,7 +984,7 @@ int bdc_apply_reflectors_noalloc(bdc_handle_t h, int trans, int m, int p, int k,
   if (a != BDC_OK) return a == 1 ? BDC_OK : a;
   const int panel = std::min(p, kBtFixedPanel);
   if (backtr_limit_bytes(m, panel, block) > kBtFixedScratchBytes) return BDC_ERR_TOO_LARGE;
-  const BtPlan plan = backtr_plan(m, p, std::min(p, kBtFixedWidth), backtr_group(block, kBtMaxGroup), true);
+  const BtPlan plan = backtr_plan(m, p, std::min(p, kBtFixedWidth), backtr_group(block, k), true);
   if (plan.bytes > kBtFixedScratchBytes) return BDC_ERR_TOO_LARGE;
   if (!h->bt_fixed) return BDC_ERR_HIP;  // the scratch address was not found at bdc_create
   DeviceGuard g(h->device);
@@ -1000,7 +1012,7 @@ int bdc_geqrf(bdc_handle_t h, int m, int n, double* A, int lda, double* tau, int
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  int rc = ensure_bt(h, m, n, block, block, &plan);
+  int rc = ensure_bt(h, m, n, block, block, (hipStream_t)stream, &plan);
   if (rc != BDC_OK) return rc;
   const size_t sb = qr_sync_bytes(kQrMaxGrid);
   if (h->qr_sync_size < sb) {
@@ -1040,7 +1052,7 @@ int bdc_orgqr(bdc_handle_t h, int m, int ncols, int k, const double* A, int lda,
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
   BtPlan plan;
-  const int rc = ensure_bt(h, m, ncols, block, backtr_group(block, kBtMaxGroup), &plan);
+  const int rc = ensure_bt(h, m, ncols, block, backtr_group(block, k), (hipStream_t)stream, &plan);
   if (rc != BDC_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_orgqr(m, ncols, k, A, lda, tau, Q, ldq, plan, h->bt_arena, st);

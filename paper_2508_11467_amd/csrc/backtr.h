@@ -35,8 +35,13 @@ struct BtPlan {
 // bytes that bound the allocation-free entry point's problems, and that any
 // problem can be run in (group = block, fixed)
 size_t backtr_limit_bytes(int m, int panel, int block);
-// reflectors applied together for a block size
-inline int backtr_group(int block, int most) { return block == kBtMaxBlock ? most : block; }
+// reflectors applied together for a block size and k reflectors in all: scratch
+// and depth slices go with it, so no more whole blocks than there are (with a
+// full group a million rows and 4 reflectors took twice the scratch)
+inline int backtr_group(int block, int k) {
+  if (block < kBtMaxBlock) return block;
+  return k <= kBtMaxBlock ? kBtMaxBlock : kBtMaxGroup;
+}
 BtPlan backtr_plan(int m, int p, int panel, int group, bool fixed);
 // rows of a tile of Y^T [C | Y] for K reflectors
 constexpr int bt_tile_rows(int K) { return K <= 32 ? 32 : 64; }

@@ -336,7 +336,7 @@ void launch_backtr(int trans, int m, int p, int k, int offset, const double* Y, 
     if (r0 >= m) continue;  // reflectors past the last row: identities
     const int rows = m - r0;
     const int bw = std::min({K, k - i0, rows});  // (also within a group)
-    const int slice = bt_slice(rows, p, K);
+    const int slice = bt_slice(rows, p, bw);
     // rows of a chunk: whole slices of W and of Y^T Y (both powers of two)
     // rows of a chunk: whole slices of W
     const int chunk = plan.fixed ? slice * std::min(kBtChunk / slice, plan.slices) : rows;

@@ -34,6 +34,7 @@ static std::map<void*, size_t> g_mem;
 static hipError_t g_last = hipSuccess;
 static int g_mallocs = 0, g_frees = 0, g_syncs = 0;
 static int g_devices = 1;
+static bool g_capturing = false;
 
 static int traffic() { return g_mallocs + g_frees + g_syncs; }
 
@@ -45,6 +46,7 @@ hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t bytes) {
   ++g_mallocs;
+  if (g_capturing) return *p = nullptr, fail(hipErrorStreamCaptureUnsupported);
   if (bytes > g_limit - g_used) return *p = nullptr, fail(hipErrorOutOfMemory);
   *p = std::malloc(1);
   g_mem[*p] = bytes;
@@ -79,6 +81,9 @@ hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hip
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { return *g = (hipGraph_t)3, hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
   return *e = (hipGraphExec_t)4, hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  return *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone, hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
@@ -208,10 +213,59 @@ static void kept() {
   }
 }
 
+// Few reflectors take the scratch and the depth slices of as many, not those of
+// a full group.
+static void few_reflectors() {
+  const int m = 1000000, p = 64;
+  for (int k : {1, 4, 20, 64}) {
+    bdc_handle_t h = handle();
+    CHECK(apply(h, m, p, k) == BDC_OK);
+    CHECK(g_scratch <= 1.25 * backtr_limit_bytes(m, p, 64));
+    CHECK(bdc_destroy(h) == BDC_OK);
+  }
+  // the products Y^T [C | Y] have a workgroup for about every CU
+  for (int k : {20, 64, 100}) {
+    const int rows = 20000, cols = 1000, tm = bt_tile_rows(k), slice = bt_slice(rows, cols, k);
+    const int slices = (rows + slice - 1) / slice, tiles = (k + tm - 1) / tm * ((cols + 127) / 128);
+    CHECK(slices * tiles >= 200);
+  }
+  // The last group of a call is no wider than what is left of it; whatever is
+  // left, its slices fit what the plan holds.
+  for (int m1 : {1, 63, 129, 1000, 4097, 20000, 300000})
+    for (int p1 : {1, 130, 1000})
+      for (int group : {1, 32, 64, 128}) {
+        const BtPlan b = backtr_plan(m1, p1, p1, group, false);
+        const size_t held = (b.pt - b.p) / p1;
+        for (int bw = 1; bw <= std::min(group, m1); ++bw)
+          for (int rows : {m1, (m1 + 1) / 2, std::min(m1, bw)}) {
+            const int s = bt_slice(rows, p1, bw);
+            CHECK((size_t)((rows + s - 1) / s) * bw <= held);
+          }
+      }
+}
+
+// Under a stream capture nothing may be allocated.  The scratch of an earlier
+// call of the same sizes serves any number of reflectors.
+static void captured() {
+  for (int m : {100, 3000, 60000}) {
+    bdc_handle_t h = handle();
+    CHECK(apply(h, m, 700, 20) == BDC_OK);
+    const int before = traffic();
+    g_capturing = true;
+    for (int k : {20, 64, 65, 2000}) CHECK(apply(h, m, 700, k) == BDC_OK);
+    CHECK(traffic() == before);
+    g_capturing = false;
+    CHECK(apply(h, m, 700, 2000) == BDC_OK && g_plan.group == kBtMaxGroup && !g_plan.fixed);
+    CHECK(bdc_destroy(h) == BDC_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
   else if (which == "kept") kept();
+  else if (which == "few_reflectors") few_reflectors();
+  else if (which == "captured") captured();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);
