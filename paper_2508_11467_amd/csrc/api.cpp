@@ -15,6 +15,7 @@
 #include <climits>
 #include <cstdint>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -67,6 +68,20 @@ struct Plan {
   void* block = nullptr;
 };
 
+// The stream that solves are captured on: one per device, shared by the handles
+// that have captured (made by the first, destroyed with the last), one capture
+// at a time.  A stream holds one of the process's few hardware queues for as
+// long as it lives: with four taken before the first grid-wide launch
+// (bdc_geqrf, bdc_gebrd), whose queue is then the fifth, every kernel beside
+// that one ran about 16 us longer (QR of 20000 x 1000 after solves with two
+// handles, of two streams each, 16.5 ms; 10.4 this way).  A stream made for each
+// capture would cost a call with new sizes 60 us.
+struct DeviceCapture {
+  std::mutex capturing;
+  hipStream_t stream = nullptr;
+  int users = 0;
+};
+
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -86,7 +101,7 @@ struct bdc_handle_s {
   bool have_call = false;
   // captured launch sequence of the current plan (all of a call but its first
   // launch, which hands over the buffers)
-  bool captures = false;  // holds the device's capture stream
+  DeviceCapture* capture = nullptr;  // the device's capture stream, once this handle has captured
   // fork and join of the captured sequence's second stream (each level's
   // rotations and gather beside its secular solve, Löwner z and vectors)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -531,36 +546,34 @@ int run_plan(bdc_handle_t h, hipStream_t st, hipStream_t side = nullptr) {
   return BDC_OK;
 }
 
-// The stream that solves are captured on: one per device, shared by the handles
-// that have captured (made by the first, destroyed with the last), one capture
-// at a time.  A stream holds one of the process's few hardware queues for as
-// long as it lives: with four taken before the first grid-wide launch
-// (bdc_geqrf, bdc_gebrd), whose queue is then the fifth, every kernel beside
-// that one ran about 16 us longer (QR of 20000 x 1000 after solves with two
-// handles, of two streams each, 16.5 ms; 10.4 this way).  A stream made for each
-// capture would cost a call with new sizes 60 us.
-struct DeviceCapture {
-  std::mutex capturing;
-  hipStream_t stream = nullptr;
-  int users = 0;
-};
-constexpr int kCaptureDevices = 64;
-DeviceCapture g_capture[kCaptureDevices];
+// the device's entry (one per device that has captured, kept until the process
+// ends), or null where there is no memory for it
+DeviceCapture* device_capture(int device) {
+  static std::mutex mu;
+  static auto* all = new (std::nothrow) std::map<int, DeviceCapture>;
+  if (!all) return nullptr;
+  std::lock_guard<std::mutex> lock(mu);
+  try {
+    return &(*all)[device];
+  } catch (const std::bad_alloc&) {
+    return nullptr;
+  }
+}
 
-bool capture_stream_hold(int device) {
-  if (device >= kCaptureDevices) return false;
-  DeviceCapture& c = g_capture[device];
-  std::lock_guard<std::mutex> lock(c.capturing);
-  if (!c.stream && hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking) != hipSuccess) {
-    c.stream = nullptr;
+bool capture_stream_hold(bdc_handle_t h) {
+  DeviceCapture* c = device_capture(h->device);
+  if (!c) return false;
+  std::lock_guard<std::mutex> lock(c->capturing);
+  if (!c->stream && hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) {
+    c->stream = nullptr;
     return false;
   }
-  ++c.users;
+  ++c->users;
+  h->capture = c;
   return true;
 }
 
-void capture_stream_drop(int device) {
-  DeviceCapture& c = g_capture[device];
+void capture_stream_drop(DeviceCapture& c) {
   std::lock_guard<std::mutex> lock(c.capturing);
   if (--c.users == 0) {
     (void)hipStreamDestroy(c.stream);
@@ -572,7 +585,7 @@ void capture_stream_drop(int device) {
 struct CaptureLease {
   std::lock_guard<std::mutex> lock;
   hipStream_t main, side = nullptr;
-  CaptureLease(int device, bool two) : lock(g_capture[device].capturing), main(g_capture[device].stream) {
+  CaptureLease(DeviceCapture& c, bool two) : lock(c.capturing), main(c.stream) {
     if (two && hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess) side = nullptr;
   }
   ~CaptureLease() {
@@ -618,11 +631,8 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
   // new ones: 130 us at n = 100, 0.5 ms at n = 16384)
   if (!h->gexec) {
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
-    if (!h->captures) {
-      if (!capture_stream_hold(h->device)) return BDC_ERR_HIP;
-      h->captures = true;
-    }
-    CaptureLease cap(h->device, h->tune.streams == 2);
+    if (!h->capture && !capture_stream_hold(h)) return BDC_ERR_HIP;
+    CaptureLease cap(*h->capture, h->tune.streams == 2);
     if (h->tune.streams == 2 && !cap.side) return BDC_ERR_HIP;
     if (!h->ev_fork && hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
     if (!h->ev_join && hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
@@ -716,7 +726,7 @@ int bdc_destroy(bdc_handle_t h) {
     DeviceGuard g(h->device);
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
     drop_graph(h);
-    if (h->captures) capture_stream_drop(h->device);
+    if (h->capture) capture_stream_drop(*h->capture);
     if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
     if (h->ev_join) (void)hipEventDestroy(h->ev_join);
     free_plan(h->plan);

@@ -33,7 +33,7 @@ static size_t g_limit = SIZE_MAX, g_used = 0;  // device memory
 static std::map<void*, size_t> g_mem;
 static hipError_t g_last = hipSuccess;
 static int g_mallocs = 0, g_frees = 0, g_syncs = 0;
-static int g_devices = 1;
+static int g_devices = 1, g_streams = 0;
 static bool g_capturing = false;
 
 static int traffic() { return g_mallocs + g_frees + g_syncs; }
@@ -74,7 +74,10 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 0.0f, hipSuccess; }
-hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)2, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  ++g_streams;
+  return *s = (hipStream_t)2, hipSuccess;
+}
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
@@ -260,12 +263,26 @@ static void captured() {
   }
 }
 
+// Solves are captured on every device that there is.
+static void many_devices() {
+  g_devices = 100;
+  for (int device : {0, 63, 64, 99}) {
+    bdc_handle_t a = handle(0, device), b = handle(0, device);
+    double out[3];
+    const int before = g_streams;
+    for (bdc_handle_t h : {a, b, a}) CHECK(bdc_svd(h, 100, out, out, out, out + 1, out + 2, nullptr) == BDC_OK);
+    CHECK(g_streams == before + 1);  // one capture stream for the device's handles
+    CHECK(bdc_destroy(a) == BDC_OK && bdc_destroy(b) == BDC_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
   else if (which == "kept") kept();
   else if (which == "few_reflectors") few_reflectors();
   else if (which == "captured") captured();
+  else if (which == "many_devices") many_devices();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);
