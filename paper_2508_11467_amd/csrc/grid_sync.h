@@ -20,8 +20,11 @@
 // totals, and the totals it put when the next sum is complete (everybody has
 // taken them by then).
 //
-// Every wait is bounded: an expired wait makes the sum return false, and the
-// kernel ends.
+// Every wait is bounded, and a thread waits out the bound once: after an expired
+// wait it takes whatever is there, the next sum of its workgroup waits for
+// nothing and returns false, and the kernel ends with its work undone.  (The
+// bound is a minute or more.  All workgroups are resident once they run, so only
+// a launch that another one keeps from its CUs for that long gets there.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,7 +33,7 @@
 
 namespace bdc {
 
-constexpr unsigned kSpin = 1u << 24;   // loads of a place before a wait expires
+constexpr unsigned kSpin = 1u << 26;   // loads of a place before a wait expires
 constexpr int kGridMaxWg = 512;        // workgroups of a grid, at most
 constexpr int kGridSets = 3;
 constexpr unsigned long long kEmpty = 0x7FF9B1D5C0DE5EEDull;
@@ -50,10 +53,10 @@ __device__ inline unsigned long long grid_peek(const double* p) {
 }
 
 // the value of b, a peek at p, or of p once it is there; ok = false when the
-// wait expired
+// wait expired (with ok false already there is none)
 __device__ inline double grid_take(const double* p, unsigned long long b, bool& ok) {
   for (unsigned it = 0; b == kEmpty; ++it) {
-    if (it == kSpin) {
+    if (!ok || it == kSpin) {
       ok = false;
       break;
     }
@@ -71,14 +74,15 @@ __device__ inline void grid_settle() { asm volatile("s_waitcnt vmcnt(0)" ::: "me
 // barrier) in, totals out in the same place.  slots, totals: this sum's set;
 // prev: the last sum's totals (prev_cnt of them).  All NT threads of all G
 // workgroups call it; bad: one word of LDS, zero before the kernel's first
-// sum.  Ends with a workgroup barrier.
+// sum, not zero where a wait of the workgroup has expired.  Ends with a
+// workgroup barrier.
 template <int NT>
 __device__ inline bool grid_sum(double* slots, double* totals, double* prev, int prev_cnt, int cnt, double* v,
                                 unsigned* bad) {
   constexpr int NW = NT / 64;
   const int t = threadIdx.x, ln = t & 63, wv = t >> 6;
   const int G = gridDim.x, g = blockIdx.x;
-  bool ok = true;
+  bool ok = *bad == 0;
   for (int q = t; q < cnt; q += NT) grid_put(slots + (size_t)q * G + g, v[q]);
   // the values dealt to this workgroup
   for (int q = g + G * wv; q < cnt; q += G * NW) {

@@ -31,9 +31,8 @@
 //      columns together.
 // Panels of 32 columns of 20000 rows: 525 us with an all-reduce and three
 // passes over LDS per column, 114 us so (four all-reduces).
-// Every wait of the all-reduce is bounded (a flag reports an expired wait and
-// the kernel ends), and the launch is cooperative, so all workgroups are
-// resident.
+// Every wait of the all-reduce is bounded (the kernel ends after an expired one),
+// and the launch is cooperative, so all workgroups are resident.
 #include <algorithm>
 
 #include "bdc_internal.h"
