@@ -1090,13 +1090,19 @@ int bdc_gebrd(bdc_handle_t h, int m, int n, double* A, int lda, double* d, doubl
   if (block < 1 || block > gebrd_max_block()) return -10;
   DeviceGuard g(h->device);
   if (!g.ok) return BDC_ERR_HIP;
-  const size_t bytes = gebrd_work_bytes(m, n, block, kQrMaxGrid);
+  size_t bytes = gebrd_work_bytes(m, n, block, kQrMaxGrid);
+  if (block > 2 && !cap_admits(h, bytes)) {
+    // the places of the column and the row (24 bytes an entry) instead of two
+    // of the panel's columns (32)
+    block -= 2;
+    bytes = gebrd_work_bytes(m, n, block, kQrMaxGrid);
+  }
   if (h->brd_bytes < bytes) {
+    if (!cap_admits(h, bytes)) return BDC_ERR_NOMEM;
     if (h->have_call) (void)hipStreamSynchronize(h->last_stream);
     if (h->brd_work) (void)hipFree(h->brd_work);
     h->brd_work = nullptr;
     h->brd_bytes = 0;
-    if (h->opt.workspace_cap_bytes && h->arena_bytes + bytes > h->opt.workspace_cap_bytes) return BDC_ERR_NOMEM;
     if (hipMalloc(&h->brd_work, bytes) != hipSuccess) {
       h->brd_work = nullptr;
       return BDC_ERR_NOMEM;

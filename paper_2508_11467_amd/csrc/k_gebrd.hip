@@ -44,8 +44,8 @@
 namespace bdc {
 namespace {
 
-constexpr int kBrdMaxB = 32;              // panel width, at most (2b <= 64 columns of P, Q)
-constexpr int kSlot = 2 * kBrdMaxB + 2;   // values of a sum over the grid, at most
+constexpr int kSlot = kBrdSlot;
+static_assert(kBrdSets == kGridSets && kBrdMaxWg == kGridMaxWg, "exchange places");
 
 struct BrdLds {
   double q[kSlot];              // partial sums, then totals
@@ -448,18 +448,7 @@ __global__ __launch_bounds__(256) void k_brd_clear(double* __restrict__ places, 
     grid_clear(places + e);
 }
 
-// exchange places of a panel
-size_t brd_places(int m, int n, int wgs) {
-  return (size_t)kGridSets * ((size_t)kSlot * wgs + kSlot + (size_t)m + n + 4 * kBrdMaxB);
-}
-
 }  // namespace
-
-int gebrd_max_block() { return kBrdMaxB; }
-
-size_t gebrd_work_bytes(int m, int n, int b, int max_wg) {
-  return 8 * ((size_t)m * 2 * b + (size_t)2 * b * n + brd_places(m, n, std::min(max_wg, kGridMaxWg)));
-}
 
 int launch_gebrd(int device, int m, int n, double* A, int lda, double* tauq, double* taup, double* d, double* e,
                  int b, void* work, size_t work_bytes, int max_wg, hipStream_t st) {
@@ -490,7 +479,7 @@ int launch_gebrd(int device, int m, int n, double* A, int lda, double* tauq, dou
     X.qc = X.pc + kGridSets * 2 * kBrdMaxB;
     X.x = X.qc + kGridSets * 2 * kBrdMaxB;
     X.u = X.x + (size_t)kGridSets * m;
-    const int64_t count = (int64_t)brd_places(m, n, G);
+    const int64_t count = (int64_t)gebrd_places(m, n, G);
     hipLaunchKernelGGL(k_brd_clear, dim3((unsigned)std::min<int64_t>((count + 255) / 256, 1024)), dim3(256), 0, st,
                        places, count);
     void* args[] = {&A, &lda64, &m, &n, &j0, const_cast<int*>(&bw), &P, &ldp64, &Qt, &ldq_, &tauq, &taup, &d, &e,

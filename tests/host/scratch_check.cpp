@@ -120,10 +120,9 @@ void launch_orgqr(int, int, int, const double*, int, const double*, double*, int
 void* backtr_fixed_scratch(int) { return nullptr; }
 size_t qr_sync_bytes(int) { return 4096; }
 int qr_max_block() { return 64; }
-int gebrd_max_block() { return 32; }
-size_t gebrd_work_bytes(int m, int n, int b, int) { return 16 * (size_t)b * (m + n); }
-int launch_gebrd(int, int, int, double*, int, double*, double*, double*, double*, int, void*, size_t, int,
-                 hipStream_t) {
+int launch_gebrd(int, int m, int n, double*, int, double*, double*, double*, double*, int b, void* work, size_t bytes,
+                 int max_wg, hipStream_t) {
+  CHECK(bytes == g_mem.at(work) && gebrd_work_bytes(m, n, b, max_wg) <= bytes);
   return BDC_OK;
 }
 int oz_supported(int) { return 1; }
@@ -276,6 +275,30 @@ static void many_devices() {
   }
 }
 
+// A cap that held the reduction's scratch when its exchange had no places of
+// m and n (2 x 64 groups' and 2 x 2048 workgroups' sums of 66 and a barrier's
+// state) still does.
+static void reduction_under_a_cap() {
+  for (int block : {0, 3, 32})
+    for (int m : {40, 5000, 60000, 2000000})
+      for (int n : {40, 1000}) {
+        const int b = block ? block : 32;
+        const size_t cap = 4352 + 8 * ((size_t)2 * b * m + (size_t)2 * b * n + 2 * (2048 + 64) * 66);
+        bdc_handle_t h = handle(cap);
+        int before = 0;
+        for (int round = 0; round < 2; ++round) {
+          CHECK(bdc_gebrd(h, m, n > m ? m : n, &d_arg, m, &d_arg, &d_arg, &d_arg, &d_arg, block, nullptr) == BDC_OK);
+          if (round) CHECK(traffic() == before);
+          before = traffic();
+        }
+        CHECK(bdc_destroy(h) == BDC_OK);
+        h = handle(cap / 2);
+        if (m > 5000)
+          CHECK(bdc_gebrd(h, m, n, &d_arg, m, &d_arg, &d_arg, &d_arg, &d_arg, block, nullptr) == BDC_ERR_NOMEM);
+        CHECK(bdc_destroy(h) == BDC_OK);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
@@ -283,6 +306,7 @@ int main(int argc, char** argv) {
   else if (which == "few_reflectors") few_reflectors();
   else if (which == "captured") captured();
   else if (which == "many_devices") many_devices();
+  else if (which == "reduction_under_a_cap") reduction_under_a_cap();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);

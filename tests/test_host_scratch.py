@@ -28,7 +28,8 @@ def check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["out_of_memory", "kept", "few_reflectors", "captured", "many_devices"])
+@pytest.mark.parametrize("case", ["out_of_memory", "kept", "few_reflectors", "captured", "many_devices",
+                                  "reduction_under_a_cap"])
 def test_scratch(check, case):
     r = subprocess.run([check, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "0 failures" in r.stdout, (r.stdout + r.stderr)[-3000:]
