@@ -105,6 +105,7 @@ struct bdc_handle_s {
   // fork and join of the captured sequence's second stream (each level's
   // rotations and gather beside its secular solve, Löwner z and vectors)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  hipEvent_t ev_order = nullptr;  // between calls on different streams
   hipGraphExec_t gexec = nullptr;
   struct Rec {
     int kind;
@@ -540,10 +541,7 @@ int run_plan(bdc_handle_t h, hipStream_t st, hipStream_t side = nullptr) {
       launch_final(p.dev_prob, p.dev_prob + np, p.dev_prob + 2 * np, p.dev_prob + 3 * np, p.dev_prob + 4 * np,
                    p.dev_uprob, p.dev_vprob, p.total_cols, p.total_tiles, w, st);
   }
-  if (hipGetLastError() != hipSuccess) return BDC_ERR_HIP;
-  h->last_stream = st;
-  h->have_call = true;
-  return BDC_OK;
+  return hipGetLastError() == hipSuccess ? BDC_OK : BDC_ERR_HIP;
 }
 
 // the device's entry (one per device that has captured, kept until the process
@@ -593,6 +591,26 @@ struct CaptureLease {
   }
 };
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) == hipSuccess) return c == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
+// st waits for the handle's last call where that was on another stream: the two
+// share the workspace and the place of the buffers, and a captured sequence,
+// which serves any buffers, is no longer made anew (after a wait) for a call
+// with other ones
+int after_last_stream(bdc_handle_t h, hipStream_t st) {
+  if (!h->have_call || h->last_stream == st || capturing(st)) return BDC_OK;
+  if (!h->ev_order && hipEventCreateWithFlags(&h->ev_order, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
+  if (hipEventRecord(h->ev_order, h->last_stream) == hipSuccess)
+    return hipStreamWaitEvent(st, h->ev_order, 0) == hipSuccess ? BDC_OK : BDC_ERR_HIP;
+  (void)hipGetLastError();  // that stream is gone
+  return BDC_OK;
+}
+
 int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, const double* e,
           double* sigma, double* U, double* VT, hipStream_t st) {
   DeviceGuard g(h->device);
@@ -622,7 +640,11 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
   };
   if (h->opt.timing || !h->opt.use_graph || h->harvest) {
     start_call();
-    return run_plan(h, st);
+    rc = run_plan(h, st);
+    if (rc != BDC_OK) return rc;
+    h->last_stream = st;
+    h->have_call = true;
+    return BDC_OK;
   }
   // replay the plan's captured sequence: it does not depend on the buffers,
   // which the call's first launch hands over on the device, so only new sizes
@@ -651,6 +673,8 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
       return BDC_ERR_HIP;
     }
   }
+  rc = after_last_stream(h, st);
+  if (rc != BDC_OK) return rc;
   start_call();
   if (hipGraphLaunch(h->gexec, st) != hipSuccess) return BDC_ERR_HIP;
   h->last_stream = st;
@@ -729,6 +753,7 @@ int bdc_destroy(bdc_handle_t h) {
     if (h->capture) capture_stream_drop(*h->capture);
     if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
     if (h->ev_join) (void)hipEventDestroy(h->ev_join);
+    if (h->ev_order) (void)hipEventDestroy(h->ev_order);
     free_plan(h->plan);
     if (h->arena) (void)hipFree(h->arena);
     if (h->oz_arena) (void)hipFree(h->oz_arena);
@@ -939,13 +964,6 @@ int grow_bt(bdc_handle_t h, size_t bytes) {
   }
   h->bt_bytes = bytes;
   return BDC_OK;
-}
-
-bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &c) == hipSuccess) return c == hipStreamCaptureStatusActive;
-  (void)hipGetLastError();
-  return false;
 }
 
 // scratch and plan for m rows and p columns; where the memory for large

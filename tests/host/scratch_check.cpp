@@ -35,6 +35,8 @@ static hipError_t g_last = hipSuccess;
 static int g_mallocs = 0, g_frees = 0, g_syncs = 0;
 static int g_devices = 1, g_streams = 0;
 static bool g_capturing = false;
+static hipStream_t g_synced = nullptr, g_recorded = nullptr;  // last one waited for by the host; the stream of the last event
+static std::map<std::pair<hipStream_t, hipStream_t>, int> g_waits;  // (stream waited for, waiting one)
 
 static int traffic() { return g_mallocs + g_frees + g_syncs; }
 
@@ -65,13 +67,13 @@ hipError_t hipGetLastError(void) {
   g_last = hipSuccess;
   return e;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return ++g_syncs, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t st) { return g_synced = st, ++g_syncs, hipSuccess; }
 hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
 hipError_t hipMemset(void*, int, size_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)1, hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = (hipEvent_t)1, hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t st) { return g_recorded = st, hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 0.0f, hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
@@ -79,7 +81,7 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   return *s = (hipStream_t)2, hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t, unsigned) { return g_waits[{g_recorded, st}]++, hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { return *g = (hipGraph_t)3, hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
@@ -299,6 +301,31 @@ static void reduction_under_a_cap() {
       }
 }
 
+// A solve on another stream than the last one starts after that one has ended,
+// whatever its buffers (both use the handle's workspace); on the same stream,
+// and under a capture, nothing is added.
+static void streams() {
+  hipStream_t a = (hipStream_t)16, b = (hipStream_t)32;
+  double x[6];
+  bdc_handle_t h = handle();
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, a) == BDC_OK);
+  CHECK(g_waits.empty());
+  const int before = g_syncs;
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, a) == BDC_OK);
+  CHECK(g_waits.empty() && g_syncs == before);
+  CHECK(bdc_svd(h, 100, x, x, x + 3, x + 4, x + 5, b) == BDC_OK);
+  CHECK(g_waits.count({a, b}) == 1 || (g_syncs > before && g_synced == a));
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, nullptr) == BDC_OK);
+  CHECK(g_waits.count({b, nullptr}) == 1 || g_synced == b);
+  g_waits.clear();
+  g_capturing = true;
+  const int traffic_before = traffic();
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, a) == BDC_OK);
+  CHECK(g_waits.empty() && traffic() == traffic_before);
+  g_capturing = false;
+  CHECK(bdc_destroy(h) == BDC_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
@@ -307,6 +334,7 @@ int main(int argc, char** argv) {
   else if (which == "captured") captured();
   else if (which == "many_devices") many_devices();
   else if (which == "reduction_under_a_cap") reduction_under_a_cap();
+  else if (which == "streams") streams();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);

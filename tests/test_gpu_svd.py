@@ -362,3 +362,27 @@ def test_handles_share_the_capture_stream(gpu, streams):
     c = handle()
     check(c, 50)
     c.close()
+
+
+def test_solves_on_two_streams_follow_each_other(gpu):
+    """Solves of one handle with other inputs and outputs on streams that do not
+    wait for each other: the second starts when the first has ended."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    n = 3000
+    data = [[torch.from_numpy(x).cuda() for x in make(n, 7)] for make in (inputs.near_ones, inputs.normal)]
+    s = Solver(0)
+    want = [[x.clone() for x in s.svd(d, e)] for d, e in data]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [[tuple(torch.empty_like(x) for x in w) for w in want] for _ in range(3)]
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for i, (d, e) in enumerate(data):
+            with torch.cuda.stream(streams[(rep + i) % 2]):
+                s.svd(d, e, out=outs[rep][i])
+    torch.cuda.synchronize()
+    for out in outs:
+        for got, ref in zip(out, want):
+            for x, y in zip(got, ref):
+                assert torch.equal(x, y)
+    s.close()

@@ -1,5 +1,5 @@
 """What the C entry points do with their scratch where memory is short, under a
-workspace cap and from call to call, and with many devices: api.cpp built with g++ against a small
+workspace cap and from call to call, with many devices and streams: api.cpp built with g++ against a small
 fake of the HIP runtime (tests/host/scratch_check.cpp; no GPU code)."""
 
 import os
@@ -29,7 +29,7 @@ def check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["out_of_memory", "kept", "few_reflectors", "captured", "many_devices",
-                                  "reduction_under_a_cap"])
+                                  "reduction_under_a_cap", "streams"])
 def test_scratch(check, case):
     r = subprocess.run([check, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "0 failures" in r.stdout, (r.stdout + r.stderr)[-3000:]
