@@ -83,7 +83,9 @@ typedef struct {
   int timing;                 /* 1: record per-kernel event times (bdc_get_timing); launches
                                  kernels one by one (no graph) */
   int use_graph;              /* 1 (default): capture a solve's launch sequence once per
-                                 sizes and options as a HIP graph and replay it */
+                                 sizes and options as a HIP graph and replay it (not on
+                                 a stream that the caller is capturing: there the
+                                 launches are recorded one by one) */
   int start;                  /* BDC_START_PLAIN (default) or BDC_START_LEARNED (needs
                                  bdc_mlp_set first; same stopping rule, only the
                                  first point of each root's iteration changes) */

@@ -603,7 +603,7 @@ bool capturing(hipStream_t st) {
 // which serves any buffers, is no longer made anew (after a wait) for a call
 // with other ones
 int after_last_stream(bdc_handle_t h, hipStream_t st) {
-  if (!h->have_call || h->last_stream == st || capturing(st)) return BDC_OK;
+  if (!h->have_call || h->last_stream == st || capturing(h->last_stream)) return BDC_OK;
   if (!h->ev_order && hipEventCreateWithFlags(&h->ev_order, hipEventDisableTiming) != hipSuccess) return BDC_ERR_HIP;
   if (hipEventRecord(h->ev_order, h->last_stream) == hipSuccess)
     return hipStreamWaitEvent(st, h->ev_order, 0) == hipSuccess ? BDC_OK : BDC_ERR_HIP;
@@ -638,7 +638,10 @@ int solve(bdc_handle_t h, int64_t batch, const int64_t* sizes, const double* d, 
     Timer t(h, st, kReset);
     launch_reset(h->w.ctl, h->w.st, h->w.sec, h->plan.nnodes, Io{d, e, sigma, U, VT}, st);
   };
-  if (h->opt.timing || !h->opt.use_graph || h->harvest) {
+  // (under the caller's own capture a sequence would not be recorded: it ran at
+  // once, with the last call's buffers, as the launch that hands over this
+  // call's is recorded)
+  if (h->opt.timing || !h->opt.use_graph || h->harvest || capturing(st)) {
     start_call();
     rc = run_plan(h, st);
     if (rc != BDC_OK) return rc;

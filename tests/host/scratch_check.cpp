@@ -32,6 +32,7 @@ static int fails = 0;
 static size_t g_limit = SIZE_MAX, g_used = 0;  // device memory
 static std::map<void*, size_t> g_mem;
 static hipError_t g_last = hipSuccess;
+static int g_graphs = 0, g_leaves = 0;  // sequences launched, leaf launches
 static int g_mallocs = 0, g_frees = 0, g_syncs = 0;
 static int g_devices = 1, g_streams = 0;
 static bool g_capturing = false;
@@ -92,7 +93,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
 }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return ++g_graphs, hipSuccess; }
 }
 
 // ---------------------------------------------------------------- the launchers
@@ -132,7 +133,7 @@ bool crt_supported(int) { return true; }
 int mlp_parts(int) { return 1; }
 size_t mlp_pack_bytes() { return 8; }
 void launch_reset(Ctl*, NodeState*, SecCount*, int, const Io&, hipStream_t) {}
-void launch_leaf(const LeafDesc*, int, int, const Work&, hipStream_t) {}
+void launch_leaf(const LeafDesc*, int, int, const Work&, hipStream_t) { ++g_leaves; }
 void launch_prep(const NodeDesc*, int, int, const Work&, hipStream_t) {}
 void launch_rotate(const NodeDesc*, int, int, const Work&, hipStream_t) {}
 void launch_gather(const NodeDesc*, int, int, const Work&, hipStream_t) {}
@@ -326,6 +327,25 @@ static void streams() {
   CHECK(bdc_destroy(h) == BDC_OK);
 }
 
+// A solve under the caller's own capture is recorded launch by launch: a
+// captured sequence launched there would run at once, with the last call's
+// buffers.
+static void captured_solve() {
+  double x[6];
+  bdc_handle_t h = handle();
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, nullptr) == BDC_OK);
+  CHECK(g_graphs == 1);
+  g_capturing = true;
+  g_leaves = 0;
+  const int before = traffic();
+  CHECK(bdc_svd(h, 100, x, x, x + 3, x + 4, x + 5, nullptr) == BDC_OK);
+  CHECK(g_graphs == 1 && g_leaves == 1 && traffic() == before);
+  g_capturing = false;
+  CHECK(bdc_svd(h, 100, x, x, x, x + 1, x + 2, nullptr) == BDC_OK);
+  CHECK(g_graphs == 2 && g_leaves == 1);
+  CHECK(bdc_destroy(h) == BDC_OK);
+}
+
 int main(int argc, char** argv) {
   const std::string which = argc > 1 ? argv[1] : "";
   if (which == "out_of_memory") out_of_memory();
@@ -335,6 +355,7 @@ int main(int argc, char** argv) {
   else if (which == "many_devices") many_devices();
   else if (which == "reduction_under_a_cap") reduction_under_a_cap();
   else if (which == "streams") streams();
+  else if (which == "captured_solve") captured_solve();
   else return 2;
   CHECK(g_mem.empty());
   std::printf("%s: %d failures\n", which.c_str(), fails);

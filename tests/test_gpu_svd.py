@@ -386,3 +386,37 @@ def test_solves_on_two_streams_follow_each_other(gpu):
             for x, y in zip(got, ref):
                 assert torch.equal(x, y)
     s.close()
+
+
+@pytest.mark.parametrize("n", [100, 777])
+def test_solve_captured_by_the_caller(gpu, n):
+    """A solve recorded into the caller's graph: every replay solves what the
+    input buffers hold then, with solves and synchronisations of the same handle
+    in between, and leaves the buffers of other calls alone."""
+    import torch
+    from paper_2508_11467_amd.api import Solver
+    data = [[torch.from_numpy(x).cuda() for x in inputs.uniform(n, 60 + i)] for i in range(4)]
+    s = Solver(0)
+    want = [[x.clone() for x in s.svd(d, e)] for d, e in data]
+    d, e = data[0][0].clone(), data[0][1].clone()
+    out = tuple(torch.zeros_like(x) for x in want[0])
+    last = s.svd(*data[1])
+    for x in last:
+        x.zero_()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        s.svd(d, e, out=out)
+    torch.cuda.synchronize()
+    assert all(float(x.abs().max()) == 0 for x in last + out)
+    for i in (2, 0, 3, 1, 1):
+        d.copy_(data[i][0])
+        e.copy_(data[i][1])
+        g.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, want[i]):
+            assert torch.equal(x, y)
+        for x, y in zip(s.svd(*data[(i + 1) % 4]), want[(i + 1) % 4]):
+            assert torch.equal(x, y)
+    assert all(float(x.abs().max()) == 0 for x in last)
+    s.close()

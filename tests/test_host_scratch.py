@@ -29,7 +29,7 @@ def check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["out_of_memory", "kept", "few_reflectors", "captured", "many_devices",
-                                  "reduction_under_a_cap", "streams"])
+                                  "reduction_under_a_cap", "streams", "captured_solve"])
 def test_scratch(check, case):
     r = subprocess.run([check, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "0 failures" in r.stdout, (r.stdout + r.stderr)[-3000:]
