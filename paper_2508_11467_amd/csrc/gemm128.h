@@ -23,7 +23,6 @@ namespace bdc {
 constexpr int kG128K = 16;    // slab depth
 constexpr int kG128A = 144;   // A as [k][m]: row stride (the two k rows of a half-wavefront's read 32 banks apart)
 constexpr int kG128B = 18;    // B (and a transposed A) as [n][k]: stride, 16-byte aligned
-constexpr int kG128Threads = 256;
 
 struct Gemm128Lds {
   double A[2][128 * kG128B];  // 128 * 18 = 16 * 144
@@ -166,8 +165,7 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
         }
     }
   };
-  auto step = [&](int buf) {
-    multiply(buf);
+  auto chain_step = [&] {  // after every slab
     if constexpr (CHAIN > 0)
       if ((++slabs & (CHAIN - 1)) == 0) chain_end();
   };
@@ -186,12 +184,14 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
     __syncthreads();
     for (int sl = 1; sl < nfull; ++sl) {
       load(k0 + sl * TK);
-      step(buf);
+      multiply(buf);
+      chain_step();
       buf ^= 1;
       stash(buf, last_row);
       __syncthreads();
     }
-    step(buf);
+    multiply(buf);
+    chain_step();
     buf ^= 1;
     kb += nfull * TK;
   }
@@ -199,10 +199,15 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
     load_tested(kb);
     stash(buf, false);
     __syncthreads();
-    step(buf);
+    multiply(buf);
+    chain_step();
     buf ^= 1;
   }
   chain_end();
+  auto& sum = [&]() -> auto& {
+    if constexpr (CHAIN > 0) return total;
+    else return acc;
+  }();
   // The products are taken as B^T A^T: D[i][j] of a 16x16 block sits in lane
   // j + 16 * (i % 4), register i / 4, so with i the column and j the row a
   // wavefront's access is 16 consecutive rows of four columns (whole 128-byte
@@ -227,11 +232,8 @@ __device__ inline void gemm128_tile(Gemm128Lds& sm, const double* __restrict__ A
       for (int r = 0; r < 4; ++r) {
         const int col = col0 + b * 16 + 4 * r;
         if (row >= M || col >= N) continue;
-        double v;
-        if constexpr (CHAIN > 0) v = total[a][b][r];
-        else v = acc[a][b][r];
-        if constexpr (Store::kReads) store(row, col, old[b][r], v);
-        else store(row, col, v);
+        if constexpr (Store::kReads) store(row, col, old[b][r], sum[a][b][r]);
+        else store(row, col, sum[a][b][r]);
       }
   }
 }
