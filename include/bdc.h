@@ -266,8 +266,8 @@ int bdc_step_gemm(bdc_handle_t handle, int M, int N, int K, const double* A, int
  * All pointers are device pointers; Y and tau are not written.  The
  * reflectors are applied `block` at a time (1..64; 0 = 64, of which
  * two blocks go together, or one where a workspace cap holds no more) in
- * the modified compact WY form of eq. inv_t / larft_update: T^{-1} = Y^T Y above its
- * diagonal and 1/tau_i on it (gemm), Z = Y^T C (gemm), Z = T^{-1} \ Z (trsm),
+ * the modified compact WY form of eq. inv_t / larft_update: T^{-1} = Y^T Y
+ * above its diagonal and 1/tau_i on it (gemm), Z = Y^T C (gemm), Z = T^{-1} \ Z (trsm),
  * C = C - Y Z (gemm), on the FP64 matrix cores.  Scratch is owned by the
  * handle (grown on demand).  Enqueues on `stream`; returns BDC_OK, -i for an
  * invalid argument i, BDC_ERR_NOMEM or BDC_ERR_HIP. */
@@ -277,11 +277,13 @@ int bdc_apply_reflectors(bdc_handle_t handle, int trans, int m, int p, int k, in
 
 /* bdc_apply_reflectors for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same arguments, kernels and results (bit for bit), but the
- * scratch is a fixed 32 MiB array of device memory per GPU, held until the
- * process ends, and C is transformed in panels of at most 512 columns and, where
- * the scratch asks for it, in chunks of its rows.  No
- * hipMalloc, hipFree or allocating library call is made.  Limit:
+ * hipMalloc): the same arguments, kernels and results (bit for bit, where that
+ * call has the memory for its scratch: with less it takes one block of
+ * reflectors at a time, whose sums run in another order), but the scratch is a
+ * fixed 32 MiB array of device memory per GPU, held until the process ends, and
+ * C is transformed in panels of at most 512 columns and, where the scratch asks
+ * for it, in chunks of its rows.  No hipMalloc, hipFree or allocating library
+ * call is made.  Limit:
  * 8 (m b + b^2 + 33 b max(b, min(p, 512))) + 1024 <= 32 MiB for the block
  * size b (m <= 48574 with b = 64 and p >= 512, any k); larger problems return
  * BDC_ERR_TOO_LARGE before any work is enqueued.  Every call on one GPU shares
@@ -340,9 +342,9 @@ int bdc_geqrf(bdc_handle_t handle, int m, int n, double* A, int lda, double* tau
 /* bdc_orgqr: Q (m x ncols, column-major, ld ldq >= m, device) <- the first
  * ncols columns of H_0 H_1 ... H_{k-1} (k <= ncols <= m; reflectors as
  * bdc_geqrf leaves them in A, ld lda), eq. orgqr-q: the identity multiplied
- * by the blocks of `block` reflectors (1..64; 0 = 64) from the last to the
- * first, T^{-1} of each block computed afresh (its own block size, not
- * geqrf's), block j touching only the rows and columns from its first pivot
+ * by the blocks of `block` reflectors (1..64; 0 = 64, of which two go
+ * together) from the last to the first, T^{-1} of each group computed afresh
+ * (its own block size, not geqrf's), group j touching only the rows and columns from its first pivot
  * on.  Returns BDC_OK, -i for argument i, BDC_ERR_NOMEM or BDC_ERR_HIP. */
 int bdc_orgqr(bdc_handle_t handle, int m, int ncols, int k, const double* A, int lda, const double* tau,
               double* Q, int ldq, int block, bdc_stream_t stream);

@@ -49,10 +49,10 @@ size_t backtr_limit_bytes(int m, int panel, int block) {
 
 // Scratch: the packed reflectors of a chunk, the slices of W and of Y^T Y,
 // their sums over earlier chunks, T^{-1}, its inverted diagonal blocks and Z.
-// With group = block and fixed it is never more than backtr_limit_bytes.  The
-// slices of W are those of the groups' real widths K' <= K: their number times
-// K' is at most most * K, whole * K where their size decides, else within
-// kBtSliceDoubles / p.
+// With group = block and fixed it is never more than backtr_limit_bytes.  W's
+// part holds whatever slices bt_slice gives any group of the call, also a last
+// one of fewer reflectors: never more than `most`, and more than `whole` only
+// while they take no more than kBtSliceDoubles.
 BtPlan backtr_plan(int m, int p, int panel, int group, bool fixed) {
   BtPlan b{};
   b.panel = std::max(1, std::min(panel, p));

@@ -18,16 +18,16 @@
 // bound by it and wider groups by the matrix cores; but the error grows with
 // the group, as the reflectors of a group see each other through the rounded
 // Y^T Y alone.  Against extended precision (rms, relative to blocks of 64 with
-// sums over 256 to 512 rows and one back substitution per column): groups of 512
-// with sums over up to 4096 rows 1.2 to 2 times for random reflectors, 2 to 4
-// times for nearly parallel ones; groups of 128 with the sums of Y^T [C | Y] in
-// chains of 64 rows 0.5 to 0.9 for both (200 to 40000 rows; groups of 256 up to
-// 1.25 for parallel ones).  So two 64-blocks go as one group, the triangular
+// sums over 256 to 512 rows and one back substitution per column; 200 to 40000
+// rows): groups of 512 with sums over up to 4096 rows up to 1.9 times for random
+// reflectors and up to 4 times for nearly parallel ones; groups of 128 with the
+// sums of Y^T [C | Y] in chains of 64 rows 0.45 to 0.9 and 0.65 to 0.95 (groups
+// of 256 so up to 1.0 and 1.25).  So two 64-blocks go as one group, the triangular
 // solve by 64-row blocks with inverted diagonal blocks, on the matrix cores too.
-// 8192 x 8192 with 8192 reflectors: 30.0 ms with groups of 128 (the update 14.5,
-// Y^T [C | Y] 13.4), 22.0 with 512, and 69.9 with 64 and one thread per column in
-// the solve (113 us a block, whatever its size); 3001 x 3001: 2.96, 2.23 and
-// 11.2 ms.
+// 8192 x 8192 with 8192 reflectors: 28.1 ms with groups of 128 (the update 13.8,
+// Y^T [C | Y] 12.0), 22.2 with 512, and 70.1 with 64 and one thread per column in
+// the solve (113 us a block, whatever its size); 3001 x 3001: 3.00, 2.26 and
+// 11.3 ms.
 #include <algorithm>
 #include <mutex>
 

@@ -465,9 +465,9 @@ int launch_gebrd(int device, int m, int n, double* A, int lda, double* tauq, dou
   const int ldq = 2 * b;
   for (int j0 = 0; j0 < n; j0 += b) {
     const int bw = std::min(b, n - j0);
-    // at least 16 rows per workgroup: 4096 x 4096 takes 358 ms in its panels
-    // with 32, 137 with 16 and 390 with 8 (whose passes load half of their 16
-    // columns for nothing)
+    // at least 16 rows per workgroup: 4096 x 4096 takes 195 ms with 32, 146 with
+    // 16 and 205 with 8 (whose passes load half of their 16 columns for
+    // nothing), 2000 x 2000 67, 47 and 51
     const int G = std::max(1, std::min(maxg, (m - j0 + 15) / 16));
     int rpw = (m - j0 + G - 1) / G, cpw = (n - j0 + G - 1) / G;
     int64_t lda64 = lda, ldp64 = m;
